@@ -79,6 +79,38 @@ __device__ inline bool adj_pixel(const float4 Xj, const float4 Xi, const float* 
   return true;
 }
 
+// Wave sums of eight values, reduce-scattered: at each of the first three steps a lane and its partner (lane ^ 1, ^ 2,
+// ^ 4) hold the same list, each keeps one half of it and adds the partner's copy; three full sums (lane ^ 8, ^ 16,
+// ^ 32) finish. Lane l < 8 stores the total of value slot 4 b0 + 2 b1 + b2 (bits of l): 10 adds and one store of 32 B
+// per wave and edge instead of eight full sums (48 adds) and eight single-lane stores, with which the gather's address
+// units were 73% busy (most of its vector-memory instructions were these stores).
+__device__ inline float dpp_swap4(float v) {  // the value of lane ^ 4: row_shl:4 into even quads, row_shr:4 into odd
+  const int lo = __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x104, 0xf, 0x5, true);
+  return __int_as_float(__builtin_amdgcn_update_dpp(lo, __float_as_int(v), 0x114, 0xf, 0xa, true));
+}
+
+__device__ inline void wave_store8(const float* v, int lane, float* __restrict__ out) {
+  const bool b0 = lane & 1, b1 = lane & 2, b2 = lane & 4;
+  float a[4], b[2];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const float keep = b0 ? v[k + 4] : v[k], send = b0 ? v[k] : v[k + 4];
+    a[k] = keep + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(send), 0xb1, 0xf, 0xf, true));
+  }
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const float keep = b1 ? a[k + 2] : a[k], send = b1 ? a[k] : a[k + 2];
+    b[k] = keep + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(send), 0x4e, 0xf, 0xf, true));
+  }
+  float s = (b2 ? b[1] : b[0]) + dpp_swap4(b2 ? b[0] : b[1]);
+  s += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s), 0x128, 0xf, 0xf, true));  // row_ror:8
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(s), __float_as_uint(s), false, false);
+  s = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(s), __float_as_uint(s), false, false);
+  s = __uint_as_float(q[0]) + __uint_as_float(q[1]);
+  if (lane < 8) out[(b0 ? 4 : 0) + (b1 ? 2 : 0) + (b2 ? 1 : 0)] = s;
+}
+
 // Query side, gathered: block (tile, k) owns 2048 pixels of keyframe k and walks the edges that end in
 // k (j = k). Per pixel it sums dE/dX_k = (s_ij R_ij)^T dE/dx and the j half of dE/dC over those edges in
 // registers and stores them once (zeros where nothing contributes); per (edge, tile) it leaves the
@@ -112,7 +144,7 @@ __global__ __launch_bounds__(kAdjThreads) void k_adjoint_gather_j(
 #pragma unroll
     for (int r = 0; r < 12; ++r) M[r] = xf[e].m[r];
     const int32_t* idx = idx_arena + E.idx_off;
-    float g7[7] = {0, 0, 0, 0, 0, 0, 0};
+    float g8[8] = {0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
     for (int u = 0; u < kAdjPPT; ++u) {
       const int n = tile * kAdjThreads * kAdjPPT + u * kAdjThreads + threadIdx.x;
@@ -126,21 +158,17 @@ __global__ __launch_bounds__(kAdjThreads) void k_adjoint_gather_j(
       acc[u][1] += M[1] * o.gx[0] + M[4] * o.gx[1] + M[7] * o.gx[2];
       acc[u][2] += M[2] * o.gx[0] + M[5] * o.gx[1] + M[8] * o.gx[2];
       acc[u][3] += o.dc / (4.0f * Xj.w);
-      g7[0] += o.gx[0];
-      g7[1] += o.gx[1];
-      g7[2] += o.gx[2];
-      g7[3] += o.x[1] * o.gx[2] - o.x[2] * o.gx[1];
-      g7[4] += o.x[2] * o.gx[0] - o.x[0] * o.gx[2];
-      g7[5] += o.x[0] * o.gx[1] - o.x[1] * o.gx[0];
-      g7[6] += o.x[0] * o.gx[0] + o.x[1] * o.gx[1] + o.x[2] * o.gx[2];
+      g8[0] += o.gx[0];
+      g8[1] += o.gx[1];
+      g8[2] += o.gx[2];
+      g8[3] += o.x[1] * o.gx[2] - o.x[2] * o.gx[1];
+      g8[4] += o.x[2] * o.gx[0] - o.x[0] * o.gx[2];
+      g8[5] += o.x[0] * o.gx[1] - o.x[1] * o.gx[0];
+      g8[6] += o.x[0] * o.gx[0] + o.x[1] * o.gx[1] + o.x[2] * o.gx[2];
     }
     // one partial per wave and edge, summed in a fixed order by the edge finalize
     float* pw = part7 + ((int64_t(e) * stride + tile) * kAdjWaves + (threadIdx.x >> 6)) * 8;
-#pragma unroll
-    for (int c = 0; c < 7; ++c) {
-      const float v = wave_sum_to_lane63(g7[c]);
-      if ((threadIdx.x & 63) == 63) pw[c] = v;
-    }
+    wave_store8(g8, threadIdx.x & (kWave - 1), pw);
   }
 #pragma unroll
   for (int u = 0; u < kAdjPPT; ++u) {
@@ -347,11 +375,7 @@ __global__ __launch_bounds__(kAdjThreads) void k_adjoint_gather(
     // one partial per wave and edge (the waves of the block never wait for each other), summed in a
     // fixed order by the edge finalize
     float* pw = part7 + ((int64_t(e) * stride + tile) * kAdjWaves + (threadIdx.x >> 6)) * 8;
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      const float v = wave_sum_to_lane63(g8[c]);
-      if ((threadIdx.x & 63) == 63) pw[c] = v;
-    }
+    wave_store8(g8, threadIdx.x & (kWave - 1), pw);
   }
   for (int q = q0; q < q1; ++q) {  // gathered side: pixel m of this keyframe, the query pixels matched to it
     const int code = node_adj[q];
