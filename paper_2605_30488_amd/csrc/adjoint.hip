@@ -21,7 +21,7 @@ namespace ds3 {
 
 constexpr int kAdjThreads = 256;
 constexpr int kAdjWaves = kAdjThreads / kWave;  // per-edge partials are written per wave (no block barrier)
-constexpr int kAdjPPT = 2;  // 65 VGPRs, 7 waves per SIMD in the gather (4: 99 VGPRs and 15% slower; 1: block reductions dominate)
+constexpr int kAdjPPT = 2;  // 58 VGPRs, 8 waves per SIMD in the gather (4, at 99 VGPRs, was 15% slower; 1: the wave sums dominate)
 
 // Forward pass and cotangents of one match (n of j, m of i), scaled by dcost. Returns false for the
 // pixels the cost skips (holes, zero ranges, bad confidences, non-finite values).
@@ -29,8 +29,6 @@ struct AdjPix {
   float x[3];    // T_ij X_j[n]
   float gx[3];   // dE/dx
   float gam[4];  // dE/de
-  float pi[3];   // psi(X_i[m])
-  float rdi;     // 1 / |X_i[m]|
   float dc;      // sum_c w_c r_c^2
   float rho;     // Huber cost of the four components (not scaled by dcost)
 };
@@ -50,11 +48,7 @@ __device__ inline bool adj_pixel(const float4 Xj, const float4 Xi, const float* 
   const float rd = rsqrtf(d2), rdi = rsqrtf(di2);
   const float d = d2 * rd, di = di2 * rdi;
   const float p[3] = {x0 * rd, x1 * rd, x2 * rd};
-  o.pi[0] = Xi.x * rdi;
-  o.pi[1] = Xi.y * rdi;
-  o.pi[2] = Xi.z * rdi;
-  o.rdi = rdi;
-  const float e4[4] = {p[0] - o.pi[0], p[1] - o.pi[1], p[2] - o.pi[2], d - di};
+  const float e4[4] = {p[0] - Xi.x * rdi, p[1] - Xi.y * rdi, p[2] - Xi.z * rdi, d - di};
   const float sq = __builtin_amdgcn_sqrtf(__builtin_amdgcn_sqrtf(cc));
   const float isg[4] = {k.inv_sr, k.inv_sr, k.inv_sr, k.inv_sd};
   float dc = 0.0f, rho = 0.0f;
@@ -76,6 +70,44 @@ __device__ inline bool adj_pixel(const float4 Xj, const float4 Xi, const float* 
   o.x[0] = x0;
   o.x[1] = x1;
   o.x[2] = x2;
+  return true;
+}
+
+// The gathered side of one match alone: dE/dX_i[m] into g and sum_c w_c r_c^2 into dc, scaled by dcost; false for the
+// pixels the cost skips. w r is r clamped to +-kappa (one median instruction instead of a reciprocal, a minimum and two
+// products), and the whitening 1/sigma enters once per row kind: about 60 instructions instead of 95 (gather of the
+// 4000-edge graph 4.95 -> 4.78 ms).
+__device__ inline bool adj_gathered(const float4 Xj, const float4 Xi, const float* M, const GnConst& k, float dcost,
+                                    float* g, float& dc) {
+  const float x0 = fmaf(M[0], Xj.x, fmaf(M[1], Xj.y, fmaf(M[2], Xj.z, M[9])));
+  const float x1 = fmaf(M[3], Xj.x, fmaf(M[4], Xj.y, fmaf(M[5], Xj.z, M[10])));
+  const float x2 = fmaf(M[6], Xj.x, fmaf(M[7], Xj.y, fmaf(M[8], Xj.z, M[11])));
+  const float d2 = fmaf(x0, x0, fmaf(x1, x1, x2 * x2));
+  const float di2 = fmaf(Xi.x, Xi.x, fmaf(Xi.y, Xi.y, Xi.z * Xi.z));
+  const float dj2 = fmaf(Xj.x, Xj.x, fmaf(Xj.y, Xj.y, Xj.z * Xj.z));
+  const float cc = Xi.w * Xj.w;
+  const float mn = fminf(fminf(d2, di2), dj2);
+  const float sum = (d2 + di2) + (dj2 + cc);
+  if (!(mn > 1e-18f) || !(cc >= 0.0f) || !(sum < __builtin_huge_valf())) return false;
+  const float rd = rsqrtf(d2), rdi = rsqrtf(di2);
+  const float p[3] = {Xi.x * rdi, Xi.y * rdi, Xi.z * rdi};
+  const float sq = __builtin_amdgcn_sqrtf(__builtin_amdgcn_sqrtf(cc));
+  const float sr = sq * k.inv_sr, sd = sq * k.inv_sd;
+  const float r[4] = {sr * fmaf(x0, rd, -p[0]), sr * fmaf(x1, rd, -p[1]), sr * fmaf(x2, rd, -p[2]),
+                      sd * fmaf(d2, rd, -(di2 * rdi))};
+  float gam[4];
+  dc = 0.0f;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const float wr = __builtin_amdgcn_fmed3f(r[c], -k.kappa, k.kappa);
+    dc = fmaf(wr, r[c], dc);
+    gam[c] = wr * (c < 3 ? sr : sd);
+  }
+  dc *= dcost;
+  // -((gam - psi (psi . gam)) / d_i + gam_range psi) = psi ((psi . gam) / d_i - gam_range) - gam / d_i
+  const float f = fmaf(p[0], gam[0], fmaf(p[1], gam[1], p[2] * gam[2])) * rdi - gam[3];
+#pragma unroll
+  for (int c = 0; c < 3; ++c) g[c] = dcost * fmaf(p[c], f, -gam[c] * rdi);
   return true;
 }
 
@@ -185,11 +217,17 @@ __global__ __launch_bounds__(kAdjThreads) void k_adjoint_gather_j(
 // Gathered side, scattered: the matches of one tile of an edge add dE/dX_i[m] and the i half of dE/dC
 // with float atomics (several matches can land on one pixel of i, and a keyframe is the gathered side of
 // several edges). Runs after k_adjoint_gather_j, whose plain stores it accumulates onto.
+// The atomics are performed at the memory side, line by line, so their cost is the cache lines an instruction touches:
+// a wave's 64 gradients are regrouped through LDS so that its three instructions each cover 21 pixels' consecutive
+// components (4 lines of 64 B where the matches are consecutive) instead of one component of 64 pixels (12 lines):
+// 424 -> 224 us for 5.9 M matches of 40 edges in float32.
 template <int DT>
 __global__ __launch_bounds__(kAdjThreads) void k_adjoint_scatter_i(
     const void* __restrict__ arena, const EdgeDev* __restrict__ edges, const EdgeXf* __restrict__ xf,
     const int32_t* __restrict__ idx_arena, GnConst k, float dcost, float* __restrict__ grad_xyz,
     float* __restrict__ grad_conf) {
+  __shared__ float sg[kAdjWaves][3 * kWave];
+  __shared__ int32_t sm[kAdjWaves][kWave];
   const int e = blockIdx.y;
   const EdgeDev E = edges[e];
   const int tile = blockIdx.x;
@@ -199,21 +237,37 @@ __global__ __launch_bounds__(kAdjThreads) void k_adjoint_scatter_i(
 #pragma unroll
   for (int q = 0; q < 12; ++q) M[q] = xf[e].m[q];
   const int32_t* idx = idx_arena + E.idx_off;
-#pragma unroll 2
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  float* __restrict__ wg = sg[wave];
+  int32_t* __restrict__ wm = sm[wave];
+  float* __restrict__ gi = grad_xyz + 3 * E.off_i;
+#pragma unroll
   for (int u = 0; u < kAdjPPT; ++u) {
     const int64_t n = int64_t(tile) * kAdjThreads * kAdjPPT + int64_t(u) * kAdjThreads + threadIdx.x;
-    if (n >= E.npx_j) continue;
-    const int32_t m = idx[n];
-    if (m < 0 || m >= E.npx_i) continue;
-    const float4 Xj = Px<DT>::load(arena, E.off_j + n);
-    const float4 Xi = Px<DT>::load(arena, E.off_i + m);
-    AdjPix o;
-    if (!adj_pixel(Xj, Xi, M, k, dcost, o)) continue;
-    const float pgi = o.pi[0] * o.gam[0] + o.pi[1] * o.gam[1] + o.pi[2] * o.gam[2];
-    float* gi = grad_xyz + 3 * (E.off_i + m);
+    int32_t m = (n < E.npx_j) ? idx[n] : -1;
+    if (m >= E.npx_i) m = -1;
+    if (m >= 0) {
+      const float4 Xj = Px<DT>::load(arena, E.off_j + n);
+      const float4 Xi = Px<DT>::load(arena, E.off_i + m);
+      float g[3], dc;
+      if (adj_gathered(Xj, Xi, M, k, dcost, g, dc)) {
+        wg[3 * lane] = g[0];
+        wg[3 * lane + 1] = g[1];
+        wg[3 * lane + 2] = g[2];
+        atomicAdd(grad_conf + E.off_i + m, dc / (4.0f * Xi.w));
+      } else {
+        m = -1;
+      }
+    }
+    wm[lane] = m;
+    __builtin_amdgcn_wave_barrier();  // a wave's LDS writes are ordered before its reads
 #pragma unroll
-    for (int a = 0; a < 3; ++a) atomicAdd(gi + a, -((o.gam[a] - o.pi[a] * pgi) * o.rdi + o.gam[3] * o.pi[a]));
-    atomicAdd(grad_conf + E.off_i + m, o.dc / (4.0f * Xi.w));
+    for (int r = 0; r < 3; ++r) {
+      const int q = r * kWave + lane, px = q / 3;
+      const int32_t mp = wm[px];
+      if (mp >= 0) atomicAdd(gi + 3 * int64_t(mp) + (q - 3 * px), wg[q]);
+    }
+    __builtin_amdgcn_wave_barrier();
   }
 }
 
@@ -302,11 +356,16 @@ __global__ __launch_bounds__(256) void k_inv_sort(const EdgeDev* __restrict__ ed
   }
 }
 
-// Cost and adjoint in one gather pass over a fixed graph: block (tile, k) owns 2048 pixels of keyframe
+// Cost and adjoint in one gather pass over a fixed graph: block (tile, k) owns 512 pixels of keyframe
 // k. For the edges that end in k it walks the matches of its pixels (query side, as in
 // k_adjoint_gather_j, plus the Huber cost in slot 7 of the tile pieces); for the edges that start in k
 // it walks, per pixel m, the list of query pixels matched to m (gathered side). Both sides are summed in
 // registers in a fixed order and stored once: no atomics, bitwise reproducible.
+// It moves 22 GB for the 4000-edge graph at close to a copy's rate, with the vector units half busy. Per edge, a wave
+// waits for its match words and then for the pixels they name; the words of the next edge are loaded before the
+// current one is computed, and what is used once (words, stored gradients) passes the caches by: 5.40 -> 4.95 ms.
+// Also loading the next edge's pixels early was slower (5.7 ms), and placing neighbouring tiles on one XCD cut the
+// bytes by 18% but not the time.
 template <int DT>
 __global__ __launch_bounds__(kAdjThreads) void k_adjoint_gather(
     const void* __restrict__ arena, const EdgeDev* __restrict__ edges, const EdgeXf* __restrict__ xf,
@@ -324,45 +383,58 @@ __global__ __launch_bounds__(kAdjThreads) void k_adjoint_gather(
   const int p0 = tile * kAdjThreads * kAdjPPT + threadIdx.x;
   raw_t xr[kAdjPPT];
   float acc[kAdjPPT][4];
+  bool any[kAdjPPT];  // a match contributed
 #pragma unroll
   for (int u = 0; u < kAdjPPT; ++u) {
     const int n = p0 + u * kAdjThreads;
     xr[u] = Px<DT>::load_raw(arena, off + (n < npx ? n : 0));
 #pragma unroll
     for (int c = 0; c < 4; ++c) acc[u][c] = 0.0f;
+    any[u] = false;
   }
   const int q0 = node_ptr[kf], q1 = node_ptr[kf + 1];
-  for (int q = q0; q < q1; ++q) {  // query side: pixel n of this keyframe, its match m in i
-    const int code = node_adj[q];
-    if (!(code & 1)) continue;
-    const int e = code >> 1;
+  // the next incident edge on one side (1: this keyframe is j, 0: it is i), and its match words for this thread's pixels
+  auto next_edge = [&](int q, int side) {
+    while (q < q1 && (node_adj[q] & 1) != side) ++q;
+    return q;
+  };
+  auto load_words = [&](const int32_t* __restrict__ w, int32_t* out) {
+#pragma unroll
+    for (int u = 0; u < kAdjPPT; ++u) {
+      const int n = p0 + u * kAdjThreads;
+      out[u] = (n < npx) ? __builtin_nontemporal_load(w + n) : -1;
+    }
+  };
+  int32_t word[kAdjPPT], ahead[kAdjPPT];
+  // query side: pixel n of this keyframe, its match m in i
+  int q = next_edge(q0, 1);
+  if (q < q1) load_words(idx_arena + edges[node_adj[q] >> 1].idx_off, word);
+  while (q < q1) {
+    const int e = node_adj[q] >> 1;
     const EdgeDev E = edges[e];
     float M[12];
 #pragma unroll
     for (int r = 0; r < 12; ++r) M[r] = xf[e].m[r];
-    const int32_t* idx = idx_arena + E.idx_off;
-    // every load of the edge first: the matches, then the matched pixels
     int32_t mm[kAdjPPT];
-#pragma unroll
-    for (int u = 0; u < kAdjPPT; ++u) {
-      const int n = p0 + u * kAdjThreads;
-      mm[u] = (n < npx) ? idx[n] : -1;
-      mm[u] = (mm[u] < E.npx_i) ? mm[u] : -1;
-    }
     raw_t xi[kAdjPPT];
 #pragma unroll
-    for (int u = 0; u < kAdjPPT; ++u) xi[u] = Px<DT>::load_raw(arena, E.off_i + (mm[u] >= 0 ? mm[u] : 0));
+    for (int u = 0; u < kAdjPPT; ++u) {
+      mm[u] = (word[u] < E.npx_i) ? word[u] : -1;
+      xi[u] = Px<DT>::load_raw(arena, E.off_i + (mm[u] >= 0 ? mm[u] : 0));
+    }
+    q = next_edge(q + 1, 1);
+    if (q < q1) load_words(idx_arena + edges[node_adj[q] >> 1].idx_off, ahead);
     float g8[8] = {0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
     for (int u = 0; u < kAdjPPT; ++u) {
       if (mm[u] < 0) continue;
-      const float4 Xj = Px<DT>::unpack(xr[u]);
       AdjPix o;
-      if (!adj_pixel(Xj, Px<DT>::unpack(xi[u]), M, k, dcost, o)) continue;
+      if (!adj_pixel(Px<DT>::unpack(xr[u]), Px<DT>::unpack(xi[u]), M, k, dcost, o)) continue;
       acc[u][0] += M[0] * o.gx[0] + M[3] * o.gx[1] + M[6] * o.gx[2];
       acc[u][1] += M[1] * o.gx[0] + M[4] * o.gx[1] + M[7] * o.gx[2];
       acc[u][2] += M[2] * o.gx[0] + M[5] * o.gx[1] + M[8] * o.gx[2];
-      acc[u][3] += o.dc / (4.0f * Xj.w);
+      acc[u][3] += o.dc;
+      any[u] = true;
       g8[0] += o.gx[0];
       g8[1] += o.gx[1];
       g8[2] += o.gx[2];
@@ -374,62 +446,64 @@ __global__ __launch_bounds__(kAdjThreads) void k_adjoint_gather(
     }
     // one partial per wave and edge (the waves of the block never wait for each other), summed in a
     // fixed order by the edge finalize
-    float* pw = part7 + ((int64_t(e) * stride + tile) * kAdjWaves + (threadIdx.x >> 6)) * 8;
-    wave_store8(g8, threadIdx.x & (kWave - 1), pw);
+    wave_store8(g8, threadIdx.x & (kWave - 1),
+                part7 + ((int64_t(e) * stride + tile) * kAdjWaves + (threadIdx.x >> 6)) * 8);
+#pragma unroll
+    for (int u = 0; u < kAdjPPT; ++u) word[u] = ahead[u];
   }
-  for (int q = q0; q < q1; ++q) {  // gathered side: pixel m of this keyframe, the query pixels matched to it
-    const int code = node_adj[q];
-    if (code & 1) continue;
-    const int e = code >> 1;
+  // gathered side: pixel m of this keyframe, the query pixels matched to it
+  q = next_edge(q0, 0);
+  if (q < q1) load_words(inv_head + cbase[node_adj[q] >> 1], word);
+  while (q < q1) {
+    const int e = node_adj[q] >> 1;
     const EdgeDev E = edges[e];
     float M[12];
 #pragma unroll
     for (int r = 0; r < 12; ++r) M[r] = xf[e].m[r];
-    const int32_t* hd = inv_head + cbase[e];
     int h[kAdjPPT], n0[kAdjPPT];
-#pragma unroll
-    for (int u = 0; u < kAdjPPT; ++u) {
-      const int m = p0 + u * kAdjThreads;
-      h[u] = (m < npx) ? hd[m] : -1;
-      n0[u] = (h[u] >= 0) ? h[u] : ((h[u] <= -2) ? -2 - h[u] : -1);
-    }
     raw_t xj[kAdjPPT];
 #pragma unroll
-    for (int u = 0; u < kAdjPPT; ++u) xj[u] = Px<DT>::load_raw(arena, E.off_j + (n0[u] >= 0 ? n0[u] : 0));
+    for (int u = 0; u < kAdjPPT; ++u) {
+      h[u] = word[u];
+      n0[u] = (h[u] >= 0) ? h[u] : ((h[u] <= -2) ? -2 - h[u] : -1);
+      xj[u] = Px<DT>::load_raw(arena, E.off_j + (n0[u] >= 0 ? n0[u] : 0));
+    }
+    q = next_edge(q + 1, 0);
+    if (q < q1) load_words(inv_head + cbase[node_adj[q] >> 1], ahead);
+    auto gathered = [&](int u, const float4 Xj) {
+      float gi[3], dc;
+      if (!adj_gathered(Xj, Px<DT>::unpack(xr[u]), M, k, dcost, gi, dc)) return;
+#pragma unroll
+      for (int c = 0; c < 3; ++c) acc[u][c] += gi[c];
+      acc[u][3] += dc;
+      any[u] = true;
+    };
 #pragma unroll
     for (int u = 0; u < kAdjPPT; ++u) {
       if (n0[u] < 0) continue;
-      const float4 Xi = Px<DT>::unpack(xr[u]);
       // the first query pixel from the head word; the rest of a longer list (rare) from the CSR, in
       // increasing n as before
-      int x = 0, xe = 0;
-      if (h[u] <= -2) {
-        const int32_t* lo = inv_off + obase[e];
-        const int m = p0 + u * kAdjThreads;
-        x = lo[m];
-        xe = lo[m + 1];
-      }
+      gathered(u, Px<DT>::unpack(xj[u]));
+      if (h[u] > -2) continue;
+      const int32_t* lo = inv_off + obase[e];
       const int32_t* lst = inv_src + sbase[e];
-      for (bool first = true; first || x + 1 < xe; first = false) {
-        const float4 Xj = first ? Px<DT>::unpack(xj[u]) : Px<DT>::load(arena, E.off_j + lst[++x]);
-        AdjPix o;
-        if (!adj_pixel(Xj, Xi, M, k, dcost, o)) continue;
-        const float pgi = o.pi[0] * o.gam[0] + o.pi[1] * o.gam[1] + o.pi[2] * o.gam[2];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) acc[u][c] -= (o.gam[c] - o.pi[c] * pgi) * o.rdi + o.gam[3] * o.pi[c];
-        acc[u][3] += o.dc / (4.0f * Xi.w);
-      }
+      const int m = p0 + u * kAdjThreads;
+      const int xe = lo[m + 1];
+      for (int x = lo[m] + 1; x < xe; ++x) gathered(u, Px<DT>::load(arena, E.off_j + lst[x]));
     }
+#pragma unroll
+    for (int u = 0; u < kAdjPPT; ++u) word[u] = ahead[u];
   }
 #pragma unroll
   for (int u = 0; u < kAdjPPT; ++u) {
     const int n = p0 + u * kAdjThreads;
     if (n >= npx) continue;
     float* gj = grad_xyz + 3 * (off + n);
-    gj[0] = acc[u][0];
-    gj[1] = acc[u][1];
-    gj[2] = acc[u][2];
-    grad_conf[off + n] = acc[u][3];
+    __builtin_nontemporal_store(acc[u][0], gj);
+    __builtin_nontemporal_store(acc[u][1], gj + 1);
+    __builtin_nontemporal_store(acc[u][2], gj + 2);
+    // both sides divide by this pixel's own confidence: dE/dC = sum_c w_c r_c^2 / (4 C)
+    grad_conf[off + n] = any[u] ? acc[u][3] / (4.0f * Px<DT>::unpack(xr[u]).w) : 0.0f;
   }
 }
 
