@@ -39,7 +39,6 @@ constexpr int kMaxSegPerKf = 256;  // LDS tables of the data kernel are indexed 
 constexpr int kSlots = 49;         // 7 x 7 grid-cell offsets of a boundary neighbour
 constexpr double kFix = 1099511627776.0;  // 2^40, fixed-point scale of the boundary sums
 constexpr int kDepthThreads = 256;
-constexpr int kDepthPPT = 16;      // data kernel tile = 4096 pixels of keyframe j
 
 struct DepthKf {
   int64_t off;      // arena pixel offset
@@ -355,10 +354,14 @@ __global__ __launch_bounds__(kDepthThreads) void k_slic_move(unsigned long long*
   for (int k = 0; k < 7; ++k) o[k] = 0;
 }
 
-// Final labels: global segment id, or -1 for invalid pixels and for segments with fewer than min_px pixels.
+// Final labels: global segment id, or -1 for invalid pixels and for segments with fewer than min_px pixels; and the
+// same as 16-bit slots of the keyframe (kNoSlot for -1), which the data kernel gathers.
+constexpr uint32_t kNoSlot = 0xffffu;
+
 __global__ __launch_bounds__(kDepthThreads) void k_label_finalize(const DepthKf* __restrict__ kfs,
                                                                   const int32_t* __restrict__ cnt, int min_px,
                                                                   int32_t* __restrict__ label,
+                                                                  uint16_t* __restrict__ slot,
                                                                   uint8_t* __restrict__ seg_valid) {
   const DepthKf K = kfs[blockIdx.y];
   const int p = blockIdx.x * kDepthThreads + threadIdx.x;
@@ -366,8 +369,9 @@ __global__ __launch_bounds__(kDepthThreads) void k_label_finalize(const DepthKf*
   if (p >= K.H * K.W) return;
   const int64_t gp = K.off + p;
   const int l = label[gp];
-  if (l < 0) return;
-  label[gp] = cnt[K.seg_base + l] >= min_px ? K.seg_base + l : -1;
+  const bool keep = l >= 0 && cnt[K.seg_base + l] >= min_px;
+  if (l >= 0) label[gp] = keep ? K.seg_base + l : -1;
+  slot[gp] = uint16_t(keep ? uint32_t(l) : kNoSlot);
 }
 
 // ---- boundary table -------------------------------------------------------------------------------------
@@ -492,24 +496,52 @@ struct DepthEdge {
   int32_t npx_i, npx_j;
   int32_t base_i, base_j;  // first global segment id of keyframes i and j
   int32_t tile0, n_tiles;
+  int32_t W_j, pad;
 };
 
 // One block per (edge, tile of keyframe j): data-term sums of the segments it touches, flushed with float64
 // atomics; the block's cost into its partial. The scale factors exp(eta) of both keyframes' segments are
-// formed once per block into LDS. A thread takes groups of kGrp consecutive pixels of j: all loads of a
-// group are issued together (matches, both points, both labels), and
-// consecutive matches of one segment (the usual case: segments are tens of pixels wide and neighbouring
-// matches land in neighbouring pixels of i) are summed in registers before one LDS add per run.
-constexpr int kGrp = 4;
+// formed once per block into LDS. A block takes 64 x 64 pixels of j, a wave 64 columns by 16 rows, one row per step, so
+// that every load, the gathers through the matches among them, covers few cache lines, and a lane goes down one column,
+// where it stays in one segment of either keyframe for tens of rows (segments are that tall, and neighbouring matches
+// land in neighbouring pixels of i): it sums in registers and adds to LDS when its segment changes. What the lanes hold
+// at the end is summed over runs of 16 lanes first, since LDS adds to one address queue. 800 edges with 126.6 M pixels in
+// bfloat16: 0.48 ms, 2.3 GB from memory at 4.8 TB/s (matches 4 B, points 8 B and slots 2 B at both ends); with four
+// consecutive pixels per thread it took 0.70 ms, the address units busy 84% of it. Adding every match's sums through a
+// segmented scan of a 64-pixel row held the same loads back to 0.60 ms (0.35 ms without the adds).
+constexpr int kDataTile = 64;                                          // columns and rows per block
+constexpr int kDataRows = kDataTile / (kDepthThreads / kWave);         // rows per wave
+static_assert(kDataTile == kWave, "a lane per column");
 
-__device__ inline void run_flush(float* H, float* G, int base, int& cur, float& h, float& g) {
-  if (cur >= 0) {
-    atomicAdd(&H[cur - base], h);
-    atomicAdd(&G[cur - base], g);
+// One step of the segmented inclusive scan over a row of 16 lanes: adds the sums of the lane D below unless a run starts
+// in between (`head`, which then also covers that lane's reach).
+template <int D>
+__device__ inline void scan_step(int& head, float& h, float& g) {
+  constexpr int kShr = 0x110 + D;  // row_shr:D; lanes below the row read 0 (a head there is set anyway)
+  const float ph = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(h), kShr, 0xf, 0xf, true));
+  const float pg = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(g), kShr, 0xf, 0xf, true));
+  const int pf = __builtin_amdgcn_update_dpp(0, head, kShr, 0xf, 0xf, true);
+  if (!head) {
+    h += ph;
+    g += pg;
   }
-  cur = -1;
-  h = 0.0f;
-  g = 0.0f;
+  head |= pf;
+}
+
+// The sums of 64 neighbouring columns by segment slot: runs of one slot within a row of 16 lanes are summed and their
+// last lane adds them.
+__device__ inline void merge_flush(float* H, float* G, uint32_t slot, float h, float g, int lane) {
+  const uint32_t below = uint32_t(__builtin_amdgcn_update_dpp(0, int(slot), 0x111, 0xf, 0xf, true));  // row_shr:1
+  int head = ((lane & 15) == 0 || below != slot) ? 1 : 0;
+  const int next = __builtin_amdgcn_update_dpp(1, head, 0x101, 0xf, 0xf, false);  // row_shl:1, 1 past the row's end
+  scan_step<1>(head, h, g);
+  scan_step<2>(head, h, g);
+  scan_step<4>(head, h, g);
+  scan_step<8>(head, h, g);
+  if (next && slot != kNoSlot) {
+    atomicAdd(&H[slot], h);
+    atomicAdd(&G[slot], g);
+  }
 }
 
 template <int DT>
@@ -518,13 +550,14 @@ __global__ __launch_bounds__(kDepthThreads) void k_dr_data(const void* __restric
                                                            const int2* __restrict__ items,
                                                            const EdgeXf* __restrict__ xf,
                                                            const int32_t* __restrict__ idx_arena,
-                                                           const int32_t* __restrict__ label,
+                                                           const uint16_t* __restrict__ slot,
                                                            const double* __restrict__ eta, int n_seg, DepthConst dc,
                                                            double* __restrict__ Hd, double* __restrict__ gd,
                                                            float* __restrict__ cost_part) {
+  constexpr int kWaves = kDepthThreads / kWave;
   __shared__ float sHj[kMaxSegPerKf], sGj[kMaxSegPerKf], sHi[kMaxSegPerKf], sGi[kMaxSegPerKf];
   __shared__ float sEj[kMaxSegPerKf], sEi[kMaxSegPerKf];  // exp(eta) of the two keyframes' segments, eq. (8)
-  __shared__ float red[kDepthThreads / kWave];
+  __shared__ float red[kWaves];
   const int2 W = items[blockIdx.x];
   const DepthEdge E = edges[W.x];
   for (int q = threadIdx.x; q < kMaxSegPerKf; q += kDepthThreads) {
@@ -538,82 +571,97 @@ __global__ __launch_bounds__(kDepthThreads) void k_dr_data(const void* __restric
   for (int q = 0; q < 12; ++q) M[q] = xf[W.x].m[q];
   const int32_t* __restrict__ idx = idx_arena + E.idx_off;
   float cost = 0.0f;
-  int curj = -1, curi = -1;
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  const int tiles_x = (E.W_j + kDataTile - 1) / kDataTile;
+  const int ty = W.y / tiles_x;
+  const int x = (W.y - ty * tiles_x) * kDataTile + lane;
+  const int y0 = ty * kDataTile + __builtin_amdgcn_readfirstlane(wave) * kDataRows;  // first row of the wave
+  const int rows = min(kDataRows, E.npx_j / E.W_j - y0);
+  struct Pt {
+    typename Px<DT>::raw_t rj, ri;
+    uint32_t h, g;
+    int m;
+  };
+  auto load_match = [&](int k) {
+    const int m = (k < rows && x < E.W_j) ? __builtin_nontemporal_load(idx + int64_t(y0 + k) * E.W_j + x) : -1;
+    return m < E.npx_i ? m : -1;
+  };
+  // both points and slots of a match, without a branch (lanes without one read pixel 0)
+  auto load_points = [&](int k, int m) {
+    Pt P;
+    const int64_t pj = E.off_j + (m >= 0 ? int64_t(y0 + k) * E.W_j + x : 0), pi = E.off_i + max(m, 0);
+    P.m = m;
+    P.rj = Px<DT>::load_raw(arena, pj);
+    P.ri = Px<DT>::load_raw(arena, pi);
+    P.h = slot[pj];
+    P.g = slot[pi];
+    return P;
+  };
+  uint32_t sj = kNoSlot, si = kNoSlot;  // the lane's open runs in j and in i, and their sums
   float hj = 0.0f, gj = 0.0f, hi = 0.0f, gi = 0.0f;
-  const int base = W.y * (kDepthThreads * kDepthPPT);
+  // a pipeline over the rows: the points of the next row and the match words of the one after it are in flight while a
+  // row is computed
+  Pt cur = load_points(0, load_match(0));
+  int ahead = load_match(1);
 #pragma unroll 1
-  for (int k = 0; k < kDepthPPT / kGrp; ++k) {
-    const int n0 = base + (k * kDepthThreads + int(threadIdx.x)) * kGrp;
-    int m[kGrp];
-#pragma unroll
-    for (int u = 0; u < kGrp; ++u) {
-      const int n = n0 + u;
-      m[u] = (n < E.npx_j) ? idx[n] : -1;
-      if (m[u] >= E.npx_i) m[u] = -1;
-    }
-    float4 Xj[kGrp], Xi[kGrp];
-    int h[kGrp], g[kGrp];
-#pragma unroll
-    for (int u = 0; u < kGrp; ++u) {
-      h[u] = g[u] = -1;
-      if (m[u] >= 0) {
-        Xj[u] = Px<DT>::load(arena, E.off_j + n0 + u);
-        Xi[u] = Px<DT>::load(arena, E.off_i + m[u]);
-        h[u] = label[E.off_j + n0 + u];
-        g[u] = label[E.off_i + m[u]];
+  for (int k = 0; k < rows; ++k) {
+    const Pt P = cur;
+    cur = load_points(k + 1, ahead);
+    ahead = load_match(k + 2);
+    if (__ballot(P.m >= 0) == 0) continue;  // uniform per wave
+    const float4 A = Px<DT>::unpack(P.rj), B = Px<DT>::unpack(P.ri);
+    const float dj2 = fmaf(A.x, A.x, fmaf(A.y, A.y, A.z * A.z));
+    const float di2 = fmaf(B.x, B.x, fmaf(B.y, B.y, B.z * B.z));
+    const float cc = B.w * A.w;
+    const bool ok = P.m >= 0 && fminf(dj2, di2) > 1e-18f && dj2 + di2 + cc < __builtin_huge_valf() && cc >= 0.0f;
+    const bool in_j = ok && P.h != kNoSlot, in_i = ok && P.g != kNoSlot;
+    const float fh = in_j ? sEj[P.h] : 1.0f;  // exp(0) for a pixel without a segment
+    const float fg = in_i ? sEi[P.g] : 1.0f;
+    const float a0 = A.x * fh, a1 = A.y * fh, a2 = A.z * fh;  // X_j(eta), eq. (8)
+    const float b0 = B.x * fg, b1 = B.y * fg, b2 = B.z * fg;  // X_i(eta)
+    const float s = __builtin_amdgcn_sqrtf(__builtin_amdgcn_sqrtf(cc)) * dc.inv_sigma;
+    const float R0 = fmaf(M[0], a0, fmaf(M[1], a1, M[2] * a2));  // sR_ij X_j(eta)
+    const float R1 = fmaf(M[3], a0, fmaf(M[4], a1, M[5] * a2));
+    const float R2 = fmaf(M[6], a0, fmaf(M[7], a1, M[8] * a2));
+    const float r0 = s * (R0 + M[9] - b0), r1 = s * (R1 + M[10] - b1), r2 = s * (R2 + M[11] - b2);
+    const float e0 = fabsf(r0), e1 = fabsf(r1), e2 = fabsf(r2);
+    const float w0 = fminf(1.0f, dc.kappa * __builtin_amdgcn_rcpf(e0));
+    const float w1 = fminf(1.0f, dc.kappa * __builtin_amdgcn_rcpf(e1));
+    const float w2 = fminf(1.0f, dc.kappa * __builtin_amdgcn_rcpf(e2));
+    const float t0 = w0 * e0, t1 = w1 * e1, t2 = w2 * e2;
+    const float rho = t0 * fmaf(-0.5f, t0, e0) + t1 * fmaf(-0.5f, t1, e1) + t2 * fmaf(-0.5f, t2, e2);
+    cost += ok ? rho : 0.0f;
+    if (in_j && P.h != sj) {
+      if (sj != kNoSlot) {
+        atomicAdd(&sHj[sj], hj);
+        atomicAdd(&sGj[sj], gj);
       }
+      sj = P.h;
+      hj = gj = 0.0f;
     }
-#pragma unroll
-    for (int u = 0; u < kGrp; ++u) {
-      if (m[u] < 0) continue;
-      const float4 A = Xj[u], B = Xi[u];
-      const float dj2 = fmaf(A.x, A.x, fmaf(A.y, A.y, A.z * A.z));
-      const float di2 = fmaf(B.x, B.x, fmaf(B.y, B.y, B.z * B.z));
-      const float cc = B.w * A.w;
-      if (!(fminf(dj2, di2) > 1e-18f) || !(dj2 + di2 + cc < __builtin_huge_valf()) || !(cc >= 0.0f)) continue;
-      const float fh = h[u] >= 0 ? sEj[h[u] - E.base_j] : 1.0f;  // exp(0) for a pixel without a segment
-      const float fg = g[u] >= 0 ? sEi[g[u] - E.base_i] : 1.0f;
-      const float a0 = A.x * fh, a1 = A.y * fh, a2 = A.z * fh;   // X_j(eta), eq. (8)
-      const float b0 = B.x * fg, b1 = B.y * fg, b2 = B.z * fg;   // X_i(eta)
-      const float s = __builtin_amdgcn_sqrtf(__builtin_amdgcn_sqrtf(cc)) * dc.inv_sigma;
-      const float R0 = fmaf(M[0], a0, fmaf(M[1], a1, M[2] * a2));  // sR_ij X_j(eta)
-      const float R1 = fmaf(M[3], a0, fmaf(M[4], a1, M[5] * a2));
-      const float R2 = fmaf(M[6], a0, fmaf(M[7], a1, M[8] * a2));
-      const float r0 = s * (R0 + M[9] - b0), r1 = s * (R1 + M[10] - b1), r2 = s * (R2 + M[11] - b2);
-      const float e0 = fabsf(r0), e1 = fabsf(r1), e2 = fabsf(r2);
-      const float w0 = fminf(1.0f, dc.kappa * __builtin_amdgcn_rcpf(e0));
-      const float w1 = fminf(1.0f, dc.kappa * __builtin_amdgcn_rcpf(e1));
-      const float w2 = fminf(1.0f, dc.kappa * __builtin_amdgcn_rcpf(e2));
-      const float t0 = w0 * e0, t1 = w1 * e1, t2 = w2 * e2;
-      cost += t0 * fmaf(-0.5f, t0, e0) + t1 * fmaf(-0.5f, t1, e1) + t2 * fmaf(-0.5f, t2, e2);
-      if (h[u] >= 0) {
-        if (h[u] != curj) {
-          run_flush(sHj, sGj, E.base_j, curj, hj, gj);
-          curj = h[u];
-        }
-        const float J0 = s * R0, J1 = s * R1, J2 = s * R2;
-        hj += w0 * J0 * J0 + w1 * J1 * J1 + w2 * J2 * J2;
-        gj += w0 * J0 * r0 + w1 * J1 * r1 + w2 * J2 * r2;
+    if (in_i && P.g != si) {
+      if (si != kNoSlot) {
+        atomicAdd(&sHi[si], hi);
+        atomicAdd(&sGi[si], gi);
       }
-      if (g[u] >= 0) {
-        if (g[u] != curi) {
-          run_flush(sHi, sGi, E.base_i, curi, hi, gi);
-          curi = g[u];
-        }
-        const float J0 = -s * b0, J1 = -s * b1, J2 = -s * b2;
-        hi += w0 * J0 * J0 + w1 * J1 * J1 + w2 * J2 * J2;
-        gi += w0 * J0 * r0 + w1 * J1 * r1 + w2 * J2 * r2;
-      }
+      si = P.g;
+      hi = gi = 0.0f;
     }
+    const float J0 = s * R0, J1 = s * R1, J2 = s * R2;
+    const float I0 = -s * b0, I1 = -s * b1, I2 = -s * b2;
+    hj += in_j ? w0 * J0 * J0 + w1 * J1 * J1 + w2 * J2 * J2 : 0.0f;
+    gj += in_j ? w0 * J0 * r0 + w1 * J1 * r1 + w2 * J2 * r2 : 0.0f;
+    hi += in_i ? w0 * I0 * I0 + w1 * I1 * I1 + w2 * I2 * I2 : 0.0f;
+    gi += in_i ? w0 * I0 * r0 + w1 * I1 * r1 + w2 * I2 * r2 : 0.0f;
   }
-  run_flush(sHj, sGj, E.base_j, curj, hj, gj);
-  run_flush(sHi, sGi, E.base_i, curi, hi, gi);
+  merge_flush(sHj, sGj, sj, hj, gj, lane);
+  merge_flush(sHi, sGi, si, hi, gi, lane);
   float c = wave_sum(cost);
-  if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = c;
+  if (lane == 0) red[wave] = c;
   __syncthreads();
   if (threadIdx.x == 0) {
     float t = 0.0f;
-    for (int w = 0; w < kDepthThreads / kWave; ++w) t += red[w];
+    for (int w = 0; w < kWaves; ++w) t += red[w];
     cost_part[blockIdx.x] = t;
   }
   for (int q = threadIdx.x; q < kMaxSegPerKf; q += kDepthThreads) {
@@ -628,28 +676,44 @@ __global__ __launch_bounds__(kDepthThreads) void k_dr_data(const void* __restric
   }
 }
 
-// One thread per segment: boundary and prior terms, the damped and clipped step (free segments only), and
-// the segment's share of the boundary and prior cost (each unordered pair once, at its lower id).
+// kStepLanes lanes per segment, each on a few of its boundary slots (a thread per segment walks 49 slots of its own
+// cache lines: 40 us for 43000 segments, 15 us this way): boundary and prior terms, the damped and clipped step (free
+// segments only), and the segment's share of the boundary and prior cost (each unordered pair once, at its lower id).
+// Each block also adds its share of the data kernel's cost partials and clears its segments' data sums for the next
+// iteration.
+constexpr int kStepLanes = 16;
+constexpr int kStepSegs = kDepthThreads / kStepLanes;  // segments per block
+
+__device__ inline double lanes16_sum(double v) {
+#pragma unroll
+  for (int off = kStepLanes / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
+  return v;
+}
+
 __global__ __launch_bounds__(kDepthThreads) void k_dr_step(const DepthKf* __restrict__ kfs, int n_kf,
                                                            const int32_t* __restrict__ seg_kf,
                                                            const uint8_t* __restrict__ seg_valid,
                                                            const unsigned long long* __restrict__ bsum,
                                                            const int32_t* __restrict__ bcnt,
-                                                           const double* __restrict__ Hd, const double* __restrict__ gd,
+                                                           double* __restrict__ Hd, double* __restrict__ gd,
                                                            const double* __restrict__ eta, double* __restrict__ eta_out,
-                                                           int n_seg, DepthConst dc, double* __restrict__ cost_part) {
-  const int s = blockIdx.x * kDepthThreads + threadIdx.x;
+                                                           int n_seg, DepthConst dc,
+                                                           const float* __restrict__ data_part, int n_data,
+                                                           double* __restrict__ cost_part) {
+  const int s = blockIdx.x * kStepSegs + threadIdx.x / kStepLanes;
+  const int lane = threadIdx.x % kStepLanes;
   double cost = 0.0;
-  if (s < n_seg) {
+  for (int q = blockIdx.x * kDepthThreads + threadIdx.x; q < n_data; q += gridDim.x * kDepthThreads)
+    cost += double(data_part[q]);
+  if (s < n_seg) {  // uniform per segment's lanes
     const double e = eta[s];
     double out = e;
     if (seg_valid[s]) {
       const DepthKf K = kfs[seg_kf[s]];
       const int l = s - K.seg_base;
       const int gy = l / K.nx, gx = l - gy * K.nx;
-      double H = Hd[s] + dc.lambda_prior, g = gd[s] + dc.lambda_prior * e;
-      cost += 0.5 * dc.lambda_prior * e * e;
-      for (int q = 0; q < kSlots; ++q) {
+      double H = 0.0, g = 0.0;
+      for (int q = lane; q < kSlots; q += kStepLanes) {
         const int c = bcnt[int64_t(s) * kSlots + q];
         if (c == 0) continue;
         const int hx = gx + q % 7 - 3, hy = gy + q / 7 - 3;
@@ -660,12 +724,19 @@ __global__ __launch_bounds__(kDepthThreads) void k_dr_step(const DepthKf* __rest
         g += dc.lambda_smooth * rb;
         if (s < h) cost += 0.5 * dc.lambda_smooth * rb * rb;
       }
+      H = lanes16_sum(H) + (Hd[s] + dc.lambda_prior);
+      g = lanes16_sum(g) + (gd[s] + dc.lambda_prior * e);
+      if (lane == 0) cost += 0.5 * dc.lambda_prior * e * e;
       if (!K.anchor) {
         const double d = fmin(fmax(-g / ((1.0 + dc.lambda_lm) * H), -dc.eta_max), dc.eta_max);
         out = e + d;
       }
     }
-    eta_out[s] = out;
+    if (lane == 0) {
+      eta_out[s] = out;
+      Hd[s] = 0.0;
+      gd[s] = 0.0;
+    }
   }
   __shared__ double red[kDepthThreads / kWave];
   const double c = wave_sum(cost);
@@ -678,20 +749,10 @@ __global__ __launch_bounds__(kDepthThreads) void k_dr_step(const DepthKf* __rest
   }
 }
 
-// Cost of the iteration: the data partials (float, per block) and the step partials (float64, per block)
-// summed in a fixed order into hist[it]. Also clears Hd and gd for the next iteration.
-__global__ __launch_bounds__(kDepthThreads) void k_dr_cost(const float* __restrict__ data_part, int n_data,
-                                                           const double* __restrict__ step_part, int n_step,
-                                                           double* __restrict__ hist, int it,
-                                                           double* __restrict__ Hd, double* __restrict__ gd,
-                                                           int n_seg) {
-  for (int s = blockIdx.x * kDepthThreads + threadIdx.x; s < n_seg; s += gridDim.x * kDepthThreads) {
-    Hd[s] = 0.0;
-    gd[s] = 0.0;
-  }
-  if (blockIdx.x != 0) return;
+// Cost of the iteration: the step kernel's partials summed in a fixed order into hist[it].
+__global__ __launch_bounds__(kDepthThreads) void k_dr_cost(const double* __restrict__ step_part, int n_step,
+                                                           double* __restrict__ hist, int it) {
   double acc = 0.0;
-  for (int q = threadIdx.x; q < n_data; q += kDepthThreads) acc += double(data_part[q]);
   for (int q = threadIdx.x; q < n_step; q += kDepthThreads) acc += step_part[q];
   __shared__ double red[kDepthThreads / kWave];
   const double c = wave_sum(acc);
@@ -735,6 +796,7 @@ struct DepthPlan {
   double* Ad = nullptr;
   int32_t* label = nullptr;
   uint2* feat = nullptr;
+  uint16_t* slot = nullptr;  // per pixel: segment slot of its keyframe; shares feat's memory once the labels are final
   int64_t* cen = nullptr;
   unsigned long long* sums = nullptr;  // per segment: members, then the sums of x, y and the four features
   int32_t* cnt = nullptr;
@@ -760,6 +822,7 @@ static size_t carve_depth(void* base, DepthPlan& P) {
   P.Ad = c.take<double>(49 * size_t(std::max(P.n_edges, 1)));
   P.label = c.take<int32_t>(size_t(P.n_px));
   P.feat = c.take<uint2>(size_t(P.n_px));
+  P.slot = reinterpret_cast<uint16_t*>(P.feat);
   P.cen = c.take<int64_t>(6 * size_t(P.n_seg));
   P.sums = c.take<unsigned long long>(7 * size_t(P.n_seg));
   P.cnt = c.take<int32_t>(P.n_seg);
@@ -774,7 +837,7 @@ static size_t carve_depth(void* base, DepthPlan& P) {
   P.lmin = c.take<double>(size_t(P.n_kf) * kRangeParts);
   P.lmax = c.take<double>(size_t(P.n_kf) * kRangeParts);
   P.data_part = c.take<float>(std::max(P.n_items, 1));
-  P.step_part = c.take<double>((P.n_seg + kDepthThreads - 1) / kDepthThreads);
+  P.step_part = c.take<double>((P.n_seg + kStepSegs - 1) / kStepSegs);
   P.hist = c.take<double>(1024);
   return c.used;
 }
@@ -818,7 +881,7 @@ static int depth_segment(DepthPlan& P, int slic_iters, int min_px, hipStream_t s
     DS3_TRY(check_hip(hipGetLastError(), "k_slic"));
   }
   const dim3 gfin((std::max(max_px, max_m) + kDepthThreads - 1) / kDepthThreads, P.n_kf);
-  hipLaunchKernelGGL(k_label_finalize, gfin, dim3(kDepthThreads), 0, s, P.kfs, P.cnt, min_px, P.label, P.seg_valid);
+  hipLaunchKernelGGL(k_label_finalize, gfin, dim3(kDepthThreads), 0, s, P.kfs, P.cnt, min_px, P.label, P.slot, P.seg_valid);
   DS3_TRY(check_hip(hipGetLastError(), "k_label_finalize"));
   DS3_TRY(launch_fill_u32(reinterpret_cast<unsigned*>(P.bsum), 2 * kSlots * size_t(P.n_seg), 0u, s));
   DS3_TRY(launch_fill_u32(reinterpret_cast<unsigned*>(P.bcnt), kSlots * size_t(P.n_seg), 0u, s));
@@ -922,7 +985,6 @@ int ds3_depth_plan_create(int32_t n_kf, const ds3_image* kf, const void* arena, 
   std::vector<DepthEdge> de(std::max(n_edges, 1));
   std::vector<EdgeDev> ge(std::max(n_edges, 1));
   std::vector<int2> items;
-  const int tile = kDepthThreads * kDepthPPT;
   for (int e = 0; e < n_edges; ++e) {
     const ds3_edge& Ed = edges[e];
     if (Ed.i < 0 || Ed.i >= n_kf || Ed.j < 0 || Ed.j >= n_kf || Ed.i == Ed.j || Ed.idx_offset < 0) {
@@ -938,7 +1000,10 @@ int ds3_depth_plan_create(int32_t n_kf, const ds3_image* kf, const void* arena, 
     D.base_i = P->kf_host[Ed.i].seg_base;
     D.base_j = P->kf_host[Ed.j].seg_base;
     D.tile0 = int32_t(items.size());
-    D.n_tiles = (D.npx_j + tile - 1) / tile;
+    D.W_j = kf[Ed.j].W;
+    D.pad = 0;
+    const int64_t n_tiles = int64_t((kf[Ed.j].W + kDataTile - 1) / kDataTile) * ((kf[Ed.j].H + kDataTile - 1) / kDataTile);
+    D.n_tiles = int32_t(n_tiles);
     for (int t = 0; t < D.n_tiles; ++t) items.push_back(make_int2(e, t));
     de[e] = D;
     EdgeDev G{};
@@ -989,26 +1054,26 @@ int ds3_depth_plan_run(void* plan, const double* poses, int32_t iters, double* c
   DepthPlan* P = static_cast<DepthPlan*>(plan);
   if (!P || !poses || iters < 0 || iters > 1024) return fail(DS3_EINVAL, "depth_run: bad arguments");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const int nstep = (P->n_seg + kDepthThreads - 1) / kDepthThreads;
+  const int nstep = (P->n_seg + kStepSegs - 1) / kStepSegs;
+  if (iters > 0) DS3_TRY(launch_gn_prep(poses, P->gedges, P->n_edges, P->xf, P->Ad, s));  // the poses stay fixed
   for (int it = 0; it < iters; ++it) {
-    DS3_TRY(launch_gn_prep(poses, P->gedges, P->n_edges, P->xf, P->Ad, s));
     const bool timed = data_timer && it == iters - 1;
     if (timed) DS3_TRY(timer_record(data_timer, true, s));
     if (P->n_items > 0) {
       if (P->dt == DS3_F32)
         hipLaunchKernelGGL(k_dr_data<DS3_F32>, dim3(P->n_items), dim3(kDepthThreads), 0, s, P->arena, P->edges, P->items,
-                           P->xf, P->idx, P->label, P->eta, P->n_seg, P->dc, P->Hd, P->gd, P->data_part);
+                           P->xf, P->idx, P->slot, P->eta, P->n_seg, P->dc, P->Hd, P->gd, P->data_part);
       else
         hipLaunchKernelGGL(k_dr_data<DS3_BF16>, dim3(P->n_items), dim3(kDepthThreads), 0, s, P->arena, P->edges, P->items,
-                           P->xf, P->idx, P->label, P->eta, P->n_seg, P->dc, P->Hd, P->gd, P->data_part);
+                           P->xf, P->idx, P->slot, P->eta, P->n_seg, P->dc, P->Hd, P->gd, P->data_part);
       DS3_TRY(check_hip(hipGetLastError(), "k_dr_data"));
     }
     if (timed) DS3_TRY(timer_record(data_timer, false, s));
     hipLaunchKernelGGL(k_dr_step, dim3(std::max(nstep, 1)), dim3(kDepthThreads), 0, s, P->kfs, P->n_kf, P->seg_kf,
-                       P->seg_valid, P->bsum, P->bcnt, P->Hd, P->gd, P->eta, P->eta2, P->n_seg, P->dc, P->step_part);
+                       P->seg_valid, P->bsum, P->bcnt, P->Hd, P->gd, P->eta, P->eta2, P->n_seg, P->dc, P->data_part,
+                       P->n_items, P->step_part);
     DS3_TRY(check_hip(hipGetLastError(), "k_dr_step"));
-    hipLaunchKernelGGL(k_dr_cost, dim3(std::max(1, std::min(256, nstep))), dim3(kDepthThreads), 0, s, P->data_part,
-                       P->n_items, P->step_part, nstep, P->hist, it, P->Hd, P->gd, P->n_seg);
+    hipLaunchKernelGGL(k_dr_cost, dim3(1), dim3(kDepthThreads), 0, s, P->step_part, nstep, P->hist, it);
     DS3_TRY(check_hip(hipGetLastError(), "k_dr_cost"));
     std::swap(P->eta, P->eta2);
   }
