@@ -150,9 +150,9 @@ int launch_count_valid(const EdgeDev* edges, int n_edges, const int32_t* idx_are
 // track.hip
 size_t track_state_bytes();
 int launch_track_init(const double* T_io, int n, EdgeXf* xf, double* xf64, int32_t* done, hipStream_t s);
-int launch_track_step(const EdgeDev* edges, int n, const float* partials, const double* cost64, void* states,
-                      int32_t* done, EdgeXf* xf, double* xf64, double* T_io, double* cost_out, int32_t* trials_out,
-                      int32_t* status_out, TrackConst tc, int phase, hipStream_t s);
+struct TrackIo;
+int launch_track_step(const EdgeDev* edges, int n, const float* partials, const double* cost64, const TrackIo& io,
+                      int phase, hipStream_t s);
 
 // chol.hip
 size_t chol_workspace_bytes(int n);

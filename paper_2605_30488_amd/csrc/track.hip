@@ -26,163 +26,19 @@
 #include "common.hpp"
 #include "internal.hpp"
 #include "sim3.hpp"
+#include "track_step.hpp"
 
 namespace ds3 {
 
-struct TrackState {
-  double T[8];    // kept pose
-  double Tt[8];   // trial pose the last reduction evaluated
-  double tau[7];  // the step that produced Tt
-  double H[28];   // upper triangle of H at T (row-major pairs r <= c)
-  double b[7];
-  double E;       // E_track at T
-  double lam;
-  int32_t trials, status, count, pad;
-};
-
 size_t track_state_bytes() { return sizeof(TrackState); }
 
-__device__ inline int hidx(int r, int c) { return r * 7 - (r * (r - 1)) / 2 + (c - r); }
-
-// (H + lam diag H + eps_r I) tau = -b by Cholesky with the epsilon ladder; returns the attempt used or -1
-// (tau = 0) when every attempt fails (a non-positive or non-finite pivot).
-__device__ int solve7(const double* H, const double* b, double lam, double eps0, double mult, int attempts,
-                      double* tau) {
-  double eps = eps0;
-  for (int r = 0; r < attempts; ++r, eps *= mult) {
-    double L[49];
-    for (int i = 0; i < 7; ++i)
-      for (int j = 0; j <= i; ++j) L[7 * i + j] = H[hidx(j, i)];
-    for (int i = 0; i < 7; ++i) L[8 * i] += lam * H[hidx(i, i)] + eps;
-    bool ok = true;
-    for (int j = 0; j < 7 && ok; ++j) {
-      double d = L[8 * j];
-      for (int k = 0; k < j; ++k) d -= L[7 * j + k] * L[7 * j + k];
-      if (!(d > 0.0) || !isfinite(d)) {
-        ok = false;
-        break;
-      }
-      const double ljj = sqrt(d);
-      L[8 * j] = ljj;
-      for (int i = j + 1; i < 7; ++i) {
-        double v = L[7 * i + j];
-        for (int k = 0; k < j; ++k) v -= L[7 * i + k] * L[7 * j + k];
-        L[7 * i + j] = v / ljj;
-      }
-    }
-    if (!ok) continue;
-    double y[7];
-    for (int i = 0; i < 7; ++i) {
-      double v = -b[i];
-      for (int k = 0; k < i; ++k) v -= L[7 * i + k] * y[k];
-      y[i] = v / L[8 * i];
-    }
-    for (int i = 6; i >= 0; --i) {
-      double v = y[i];
-      for (int k = i + 1; k < 7; ++k) v -= L[7 * k + i] * tau[k];
-      tau[i] = v / L[8 * i];
-    }
-    return r;
-  }
-  for (int i = 0; i < 7; ++i) tau[i] = 0.0;
-  return -1;
-}
-
-// The trial transform for the next reduction: float32 (H, g) and float64 (the cost of the accept test).
-__device__ inline void write_xf(const Sim3& T, EdgeXf* xf, double* xf64) {
-  double R[9];
-  quat_to_mat(T.q, R);
-  EdgeXf X;
-  for (int r = 0; r < 3; ++r) {
-    for (int c = 0; c < 3; ++c) {
-      xf64[3 * r + c] = T.s * R[3 * r + c];
-      X.m[3 * r + c] = float(T.s * R[3 * r + c]);
-    }
-    xf64[9 + r] = T.t[r];
-    X.m[9 + r] = float(T.t[r]);
-  }
-  for (int k = 0; k < 4; ++k) X.pad[k] = 0.0f;
-  *xf = X;
-}
-
-// phase 0: the partials hold the sums at the initial poses (T_io); later phases: at the trial poses.
-__global__ __launch_bounds__(64) void k_track_step(const EdgeDev* __restrict__ edges,
-                                                   const float* __restrict__ partials,
-                                                   const double* __restrict__ cost64,
-                                                   TrackState* __restrict__ states, int32_t* __restrict__ done,
-                                                   EdgeXf* __restrict__ xf, double* __restrict__ xf64,
-                                                   double* __restrict__ T_io,
-                                                   double* __restrict__ cost_out, int32_t* __restrict__ trials_out,
-                                                   int32_t* __restrict__ status_out, TrackConst tc, int phase) {
+// One block per problem (see track_step).
+__global__ __launch_bounds__(kStepThreads) void k_track_step(const EdgeDev* __restrict__ edges,
+                                                             const float* __restrict__ partials,
+                                                             const double* __restrict__ cost64, TrackIo io, int phase) {
   const int p = blockIdx.x;
-  const int t = threadIdx.x;
-  if (phase > 0 && done[p]) return;
-  __shared__ double S[37];
-  __shared__ double Ecost;
-  const EdgeDev E = edges[p];
-  if (t == 63) {  // the float64 cost, summed over the segments in order
-    double s = 0.0;
-    for (int k = 0; k < E.n_tiles; ++k) s += cost64[E.tile0 + k];
-    Ecost = s;
-  }
-  if (t < 37) {
-    double s = 0.0;
-    const float* q = partials + int64_t(E.tile0) * kPartial + t;
-    int k = 0;
-    for (; k + 8 <= E.n_tiles; k += 8) {  // eight loads in flight, summed in segment order
-      float v[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = q[int64_t(k + u) * kPartial];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) s += double(v[u]);
-    }
-    for (; k < E.n_tiles; ++k) s += double(q[int64_t(k) * kPartial]);
-    S[t] = s;
-  }
-  __syncthreads();
-  if (t != 0) return;
-  TrackState& st = states[p];
-  bool stop = false;
-  if (phase == 0) {
-    for (int k = 0; k < 8; ++k) st.T[k] = T_io[8 * int64_t(p) + k];
-    for (int k = 0; k < 28; ++k) st.H[k] = S[k];
-    for (int k = 0; k < 7; ++k) st.b[k] = S[28 + k];
-    st.E = Ecost;
-    st.count = int32_t(S[36] + 0.5);
-    st.lam = tc.lambda0;
-    st.trials = 0;
-    st.status = 0;
-  } else {
-    st.trials += 1;
-    if (Ecost < st.E) {  // accept: keep the trial pose and its linearisation
-      for (int k = 0; k < 8; ++k) st.T[k] = st.Tt[k];
-      for (int k = 0; k < 28; ++k) st.H[k] = S[k];
-      for (int k = 0; k < 7; ++k) st.b[k] = S[28 + k];
-      st.E = Ecost;
-      st.count = int32_t(S[36] + 0.5);
-      st.lam = fmax(st.lam * tc.lambda_down, tc.lambda_min);
-      double m = 0.0;
-      for (int k = 0; k < 7; ++k) m = fmax(m, fabs(st.tau[k]));
-      if (m < tc.step_tol) stop = true;
-    } else {
-      st.lam *= tc.lambda_up;
-    }
-    if (st.trials >= tc.max_trials) stop = true;
-  }
-  if (!stop) {
-    st.status = solve7(st.H, st.b, st.lam, tc.eps0, tc.eps_mult, tc.attempts, st.tau);
-    const Sim3 Tt = sim3_mul(sim3_exp(st.tau), sim3_load(st.T));
-    Sim3 Tn = Tt;
-    quat_normalize(Tn.q);
-    sim3_store(Tn, st.Tt);
-    write_xf(Tn, xf + p, xf64 + 12 * int64_t(p));
-  } else {
-    done[p] = 1;
-  }
-  for (int k = 0; k < 8; ++k) T_io[8 * int64_t(p) + k] = st.T[k];
-  cost_out[p] = st.E;
-  trials_out[p] = st.trials;
-  if (status_out) status_out[p] = st.status;
+  if (phase > 0 && io.done[p]) return;
+  track_step(edges[p], p, partials, cost64, io, phase);
 }
 
 // Initial transform of every problem (float32 and float64 copies of T_io) for the phase-0 reduction.
@@ -202,13 +58,10 @@ int launch_track_init(const double* T_io, int n, EdgeXf* xf, double* xf64, int32
   return check_hip(hipGetLastError(), "k_track_init");
 }
 
-int launch_track_step(const EdgeDev* edges, int n, const float* partials, const double* cost64, void* states,
-                      int32_t* done, EdgeXf* xf, double* xf64, double* T_io, double* cost_out, int32_t* trials_out,
-                      int32_t* status_out, TrackConst tc, int phase, hipStream_t s) {
+int launch_track_step(const EdgeDev* edges, int n, const float* partials, const double* cost64, const TrackIo& io,
+                      int phase, hipStream_t s) {
   if (n <= 0) return DS3_OK;
-  hipLaunchKernelGGL(k_track_step, dim3(n), dim3(64), 0, s, edges, partials, cost64,
-                     static_cast<TrackState*>(states), done, xf, xf64, T_io, cost_out, trials_out, status_out, tc,
-                     phase);
+  hipLaunchKernelGGL(k_track_step, dim3(n), dim3(kStepThreads), 0, s, edges, partials, cost64, io, phase);
   return check_hip(hipGetLastError(), "k_track_step");
 }
 
@@ -343,6 +196,7 @@ static int track_impl(const void* arena, ds3_dtype dtype, const ds3_track_proble
   tc.eps_mult = gn->eps_mult;
   tc.max_trials = tp->max_trials;
   tc.attempts = gn->max_attempts;
+  const TrackIo io{static_cast<TrackState*>(B.states), B.done, B.xf, B.xf64, T, cost_out, trials_out, status_out, tc};
   DS3_TRY(launch_gather_stream(dtype, arena, B.edges, B.items, tiles, idx_arena, seg, B.stream, B.seg_count, s));
   DS3_TRY(launch_track_init(T, n, B.xf, B.xf64, B.done, s));
   for (int phase = 0; phase <= tp->max_trials; ++phase) {
@@ -351,8 +205,7 @@ static int track_impl(const void* arena, ds3_dtype dtype, const ds3_track_proble
     DS3_TRY(launch_reduce_stream(dtype, 2, B.stream, B.seg_count, B.edges, B.items, tiles, B.xf, seg, B.partials,
                                  c, B.done, s, B.xf64, B.cost64));
     if (timed) DS3_TRY(timer_record(reduce_timer, false, s));
-    DS3_TRY(launch_track_step(B.edges, n, B.partials, B.cost64, B.states, B.done, B.xf, B.xf64, T, cost_out,
-                              trials_out, status_out, tc, phase, s));
+    DS3_TRY(launch_track_step(B.edges, n, B.partials, B.cost64, io, phase, s));
   }
   return DS3_OK;
 }
