@@ -433,8 +433,9 @@ size_t ds3_track_workspace_bytes(int32_t n, const ds3_track_problem* probs, ds3_
  * non-finite value or a negative confidence product are skipped.
  * Outputs (device): cost_out (n float64) = E_track at the returned pose, trials_out (n int32) = trial
  * steps taken, status_out (n int32, may be NULL) = ladder attempt of the last solve (-1: zero step).
- * One call gathers the matches once, then runs 1 + max_trials rounds of two launches (reduction at the
- * trial poses, LM step) with no host synchronisation; stopped problems are skipped. reduce_timer (may be
+ * One call gathers the matches once, then runs 1 + max_trials rounds (reduction at the trial
+ * poses, LM step; one launch for few segments, else two) with no host synchronisation; stopped problems are
+ * skipped. A call with a timer runs every round in two launches; reduce_timer (may be
  * NULL) is recorded around the first reduction launch (every problem active). Workspace from
  * ds3_track_workspace_bytes. */
 int ds3_track(const void* arena, ds3_dtype dtype, const ds3_track_problem* probs, int32_t n,

@@ -24,6 +24,7 @@
 #include "common.hpp"
 #include "internal.hpp"
 #include "sim3.hpp"
+#include "track_step.hpp"
 
 namespace ds3 {
 
@@ -520,6 +521,7 @@ struct Rec<DS3_BF16> {
     r.w = __builtin_nontemporal_load(&p->w);
     return r;
   }
+  __device__ static inline raw_t load_keep(const raw_t* p) { return *p; }
   __device__ static inline void unpack(const raw_t& r, float* xj, float* xi, float& sq) {
     xj[0] = bf16_lo(r.w.x); xj[1] = bf16_hi(r.w.x); xj[2] = bf16_lo(r.w.y);
     xi[0] = bf16_hi(r.w.y); xi[1] = bf16_lo(r.w.z); xi[2] = bf16_hi(r.w.z);
@@ -544,6 +546,7 @@ struct Rec<DS3_F32> {
     r.b = __builtin_nontemporal_load(&p->b);
     return r;
   }
+  __device__ static inline raw_t load_keep(const raw_t* p) { return *p; }
   __device__ static inline void unpack(const raw_t& r, float* xj, float* xi, float& sq) {
     xj[0] = r.a.x; xj[1] = r.a.y; xj[2] = r.a.z;
     xi[0] = r.a.w; xi[1] = r.b.x; xi[2] = r.b.y;
@@ -781,6 +784,155 @@ __global__ __launch_bounds__(kReduceThreads) void k_reduce_stream(const void* __
       cost64[seg] = t;
     }
   }
+}
+
+// --------------------------------------------------------------------------------------------------
+// One round of the tracker in one launch, for few problems: the reduction of k_reduce_stream<DT, .., C64> with each
+// segment's sums split over kRoles blocks, and k_track_step's work in the last block of each problem to finish.
+// A round of one 512 x 384 frame has 48 segments: 48 blocks whose waves sit alone on their SIMDs and take 15 us for 16
+// records per thread, then a second launch of one block. The blocks of a segment hold the same records in the same
+// threads and each forms part of the sums (accumulators 0..18; 19..36; the float64 cost), in the same order, so every
+// sum has the bits it has there. The block that finishes last is found with a ticket in the problem's state; nothing
+// waits for another block. Sums are published with returning exchanges at device scope, which are performed at the
+// memory side, past the XCDs' L2s: once the results are back, so is every sum, and the ticket goes after them. (Device
+// fences instead write back and invalidate a whole L2 per block: 371 us per call for one frame, 2270 us for 24.)
+// A chain bounds it: of a round's 15.5 us the sums take 6 (8.5 in the slowest block), the ticket 1, the step 6.
+// A call of one frame and its 20 rounds: 457 us in two launches per round, 338 us in this form.
+// --------------------------------------------------------------------------------------------------
+constexpr int kRoles = 3;
+
+// Stores v at p by an exchange at device scope and waits until it has been performed.
+template <class T>
+__device__ inline void publish(T* p, T v) {
+  T was = __hip_atomic_exchange(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  asm volatile("" ::"v"(was) : "memory");  // the result is waited for here
+}
+
+template <int DT, int ROLE>
+__device__ inline void round_sums(const typename Rec<DT>::raw_t* __restrict__ in, int cnt, const float* M,
+                                  const double* __restrict__ xf64, const GnConst& k, float* __restrict__ out,
+                                  double* __restrict__ cost_out, float (*lds)[37], double* lds64) {
+  using rec_t = typename Rec<DT>::raw_t;
+  constexpr int U = 4;  // records in flight per thread
+  double M64[ROLE == 2 ? 12 : 1];
+  if constexpr (ROLE == 2) {
+#pragma unroll
+    for (int q = 0; q < 12; ++q) M64[q] = xf64[q];
+  }
+  double c64 = 0.0;
+  Acc a;
+  acc_zero(a);
+  rec_t buf[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int q = u * kReduceThreads + int(threadIdx.x);
+    if (q < cnt) buf[u] = Rec<DT>::load_keep(in + q);
+  }
+#pragma unroll 1
+  for (int k0 = 0; k0 < cnt; k0 += kReduceThreads * U) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int q = k0 + u * kReduceThreads + int(threadIdx.x);
+      const rec_t r = buf[u];
+      if (q + kReduceThreads * U < cnt) buf[u] = Rec<DT>::load_keep(in + q + kReduceThreads * U);
+      if (q < cnt) {
+        float xj[3], xi[3], sq;
+        Rec<DT>::unpack(r, xj, xi, sq);
+        float x0, x1, x2;
+        transform(M, xj[0], xj[1], xj[2], x0, x1, x2);
+        const float d2 = fmaf(x0, x0, fmaf(x1, x1, x2 * x2));
+        if (d2 > 1e-18f && d2 < __builtin_huge_valf()) {
+          if constexpr (ROLE == 2) {
+            c64 += cost_f64(M64, xj, xi, sq, k);
+          } else {
+            const float di2 = fmaf(xi[0], xi[0], fmaf(xi[1], xi[1], xi[2] * xi[2]));
+            acc_core(a, x0, x1, x2, d2, xi[0], xi[1], xi[2], di2, sq, k);
+          }
+        }
+      }
+    }
+  }
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  if constexpr (ROLE == 2) {
+    const double s = wave_sum(c64);
+    if (lane == 0) lds64[wave] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      double t = 0.0;
+#pragma unroll
+      for (int w = 0; w < kReduceThreads / kWave; ++w) t += lds64[w];
+      publish(cost_out, t);
+    }
+  } else {
+    constexpr int kFirst = ROLE == 0 ? 0 : 19, kLast = ROLE == 0 ? 19 : 37;
+    float* v = reinterpret_cast<float*>(&a);
+#pragma unroll
+    for (int q = 0; q < 37; ++q)
+      if (q < kFirst || q >= kLast) v[q] = 0.0f;  // the other block's: never formed
+    int slot;
+    const float t = acc_reduce_scatter(a, lane, slot);
+    if (slot >= kFirst && slot < kLast) lds[wave][slot] = t;
+    __syncthreads();
+    if (threadIdx.x >= kFirst && threadIdx.x < kLast) {
+      float s = 0.0f;
+#pragma unroll
+      for (int w = 0; w < kReduceThreads / kWave; ++w) s += lds[w][threadIdx.x];
+      publish(out + threadIdx.x, s);
+    }
+  }
+}
+
+template <int DT>
+__global__ __launch_bounds__(kReduceThreads) void k_track_round(const void* __restrict__ stream,
+                                                                const int32_t* __restrict__ seg_count,
+                                                                const EdgeDev* __restrict__ edges,
+                                                                const WorkItem* __restrict__ items, int n_items,
+                                                                int seg_px, float* partials, GnConst k,
+                                                                double* cost64, TrackIo io, int phase) {
+  static_assert(kReduceThreads == kStepThreads, "the last block runs the step");
+  __shared__ float lds[kReduceThreads / kWave][37];
+  __shared__ double lds64[kReduceThreads / kWave];
+  __shared__ int s_last;
+  const int role = int(blockIdx.x) / n_items;
+  const WorkItem W = items[int(blockIdx.x) - role * n_items];
+  const int p = W.edge;
+  if (phase > 0 && io.done[p]) return;  // block-uniform
+  const EdgeDev E = edges[p];
+  const int seg = E.tile0 + W.tile;
+  float M[12];
+#pragma unroll
+  for (int q = 0; q < 12; ++q) M[q] = io.xf[p].m[q];
+  const int cnt = seg_count[seg];
+  const auto* in = static_cast<const typename Rec<DT>::raw_t*>(stream) + int64_t(seg) * seg_px;
+  float* out = partials + int64_t(seg) * kPartial;
+  const double* T64 = io.xf64 + 12 * int64_t(p);
+  if (role == 0)
+    round_sums<DT, 0>(in, cnt, M, T64, k, out, cost64 + seg, lds, lds64);
+  else if (role == 1)
+    round_sums<DT, 1>(in, cnt, M, T64, k, out, cost64 + seg, lds, lds64);
+  else
+    round_sums<DT, 2>(in, cnt, M, T64, k, out, cost64 + seg, lds, lds64);
+  __syncthreads();  // the block's sums have been published
+  if (threadIdx.x == 0)
+    s_last = __hip_atomic_fetch_add(&io.states[p].ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+             E.n_tiles * kRoles - 1;
+  __syncthreads();
+  if (!s_last) return;  // block-uniform
+  track_step<true>(E, p, partials, cost64, io, phase);  // also returns the ticket to zero
+}
+
+int launch_track_round(ds3_dtype dt, const void* stream, const int32_t* seg_count, const EdgeDev* edges,
+                       const WorkItem* items, int n_items, int seg_px, float* partials, GnConst c, double* cost64,
+                       const TrackIo& io, int phase, hipStream_t s) {
+  if (n_items <= 0) return DS3_OK;
+  dim3 g(n_items * kRoles), b(kReduceThreads);
+  if (dt == DS3_F32)
+    hipLaunchKernelGGL(k_track_round<DS3_F32>, g, b, 0, s, stream, seg_count, edges, items, n_items, seg_px, partials,
+                       c, cost64, io, phase);
+  else
+    hipLaunchKernelGGL(k_track_round<DS3_BF16>, g, b, 0, s, stream, seg_count, edges, items, n_items, seg_px, partials,
+                       c, cost64, io, phase);
+  return check_hip(hipGetLastError(), "k_track_round");
 }
 
 size_t stream_record_bytes(ds3_dtype dt, bool calibrated) {

@@ -115,6 +115,10 @@ int launch_gn_prep(const double* poses, const EdgeDev* edges, int n_edges, EdgeX
 int launch_edge_reduce_one(ds3_dtype dt, int ppt, const void* arena, const EdgeDev& e, int edge_id,
                            const EdgeXf* xf, const int32_t* idx_arena, float* partials, GnConst c,
                            hipStream_t s, const EdgeCal* cal = nullptr);
+struct TrackIo;
+int launch_track_round(ds3_dtype dt, const void* stream, const int32_t* seg_count, const EdgeDev* edges,
+                       const WorkItem* items, int n_items, int seg_px, float* partials, GnConst c, double* cost64,
+                       const TrackIo& io, int phase, hipStream_t s);
 // match stream of the batched form (gn.hip)
 // Calibrated mode (ecal != NULL, device, one EdgeCal per edge): float32 records of the calibrated point
 // and the target (u_m, v_m, 1/z_i[m]) whatever the arena dtype.
@@ -149,8 +153,7 @@ int launch_count_valid(const EdgeDev* edges, int n_edges, const int32_t* idx_are
 
 // track.hip
 size_t track_state_bytes();
-int launch_track_init(const double* T_io, int n, EdgeXf* xf, double* xf64, int32_t* done, hipStream_t s);
-struct TrackIo;
+int launch_track_init(const TrackIo& io, int n, hipStream_t s);
 int launch_track_step(const EdgeDev* edges, int n, const float* partials, const double* cost64, const TrackIo& io,
                       int phase, hipStream_t s);
 

@@ -4,12 +4,12 @@
 // form of eq. 7: (H + lambda diag H + eps_r I) tau = -g, T <- Exp(tau) T).
 //
 // Execution: the matches of every problem are gathered once into a match stream (the batched graph
-// step's records: X_f[n], X_k[m], (C_k C_f)^(1/4)); then 1 + max_trials rounds of two launches run with
-// no host synchronisation: the stream reduction at every problem's trial pose (the graph step's
+// step's records: X_f[n], X_k[m], (C_k C_f)^(1/4)); then 1 + max_trials rounds run with no host
+// synchronisation, each one launch for few segments and two otherwise: the stream reduction at every problem's trial pose (the graph step's
 // residual / Jacobian / Huber / Hessian kernel, one edge per problem with the keyframe at the identity,
-// so H = H_L and g = b_L), and k_track_step, one block per problem, which sums the segment partials in
+// so H = H_L and g = b_L), and the step, one block per problem, which sums the segment partials in
 // a fixed order, takes the LM decision, solves the damped 7x7 system and writes the next trial pose.
-// Problems that have stopped are skipped by both launches.
+// Problems that have stopped are skipped.
 //
 // The accept test compares E_track at two nearby poses. Near the optimum their difference falls below
 // what a float32 evaluation resolves (each whitened ray residual is a difference of unit vectors over
@@ -38,23 +38,25 @@ __global__ __launch_bounds__(kStepThreads) void k_track_step(const EdgeDev* __re
                                                              const double* __restrict__ cost64, TrackIo io, int phase) {
   const int p = blockIdx.x;
   if (phase > 0 && io.done[p]) return;
-  track_step(edges[p], p, partials, cost64, io, phase);
+  track_step<false>(edges[p], p, partials, cost64, io, phase);
 }
 
 // Initial transform of every problem (float32 and float64 copies of T_io) for the phase-0 reduction.
 __global__ void k_track_init(const double* __restrict__ T_io, int n, EdgeXf* __restrict__ xf,
-                             double* __restrict__ xf64, int32_t* __restrict__ done) {
+                             double* __restrict__ xf64, int32_t* __restrict__ done,
+                             TrackState* __restrict__ states) {
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= n) return;
   Sim3 T = sim3_load(T_io + 8 * int64_t(p));
   quat_normalize(T.q);
   write_xf(T, xf + p, xf64 + 12 * int64_t(p));
   done[p] = 0;
+  states[p].ticket = 0;
 }
 
-int launch_track_init(const double* T_io, int n, EdgeXf* xf, double* xf64, int32_t* done, hipStream_t s) {
+int launch_track_init(const TrackIo& io, int n, hipStream_t s) {
   if (n <= 0) return DS3_OK;
-  hipLaunchKernelGGL(k_track_init, dim3((n + 63) / 64), dim3(64), 0, s, T_io, n, xf, xf64, done);
+  hipLaunchKernelGGL(k_track_init, dim3((n + 63) / 64), dim3(64), 0, s, io.T_io, n, io.xf, io.xf64, io.done, io.states);
   return check_hip(hipGetLastError(), "k_track_init");
 }
 
@@ -73,6 +75,12 @@ int launch_track_step(const EdgeDev* edges, int n, const float* partials, const 
 namespace ds3 {
 
 constexpr int kTrackPPT = 16;  // segment = 4096 frame pixels
+
+// Calls with at most this many segments run each round as one launch of three blocks per segment (k_track_round).
+// us per call, 512 x 384 float32 frames of 48 segments, one launch against two: 338 to 457 (1 frame), 330 to 439 (2),
+// 391 to 460 (4), 491 to 506 (6), 530 to 509 (8). Beyond one block per CU the records that each role reads again cost
+// more than the launch.
+constexpr int kRoundItems = 256;
 
 struct TrackBuffers {
   EdgeDev* edges;
@@ -198,8 +206,13 @@ static int track_impl(const void* arena, ds3_dtype dtype, const ds3_track_proble
   tc.attempts = gn->max_attempts;
   const TrackIo io{static_cast<TrackState*>(B.states), B.done, B.xf, B.xf64, T, cost_out, trials_out, status_out, tc};
   DS3_TRY(launch_gather_stream(dtype, arena, B.edges, B.items, tiles, idx_arena, seg, B.stream, B.seg_count, s));
-  DS3_TRY(launch_track_init(T, n, B.xf, B.xf64, B.done, s));
+  DS3_TRY(launch_track_init(io, n, s));
   for (int phase = 0; phase <= tp->max_trials; ++phase) {
+    if (tiles <= kRoundItems && !reduce_timer) {
+      DS3_TRY(launch_track_round(dtype, B.stream, B.seg_count, B.edges, B.items, tiles, seg, B.partials, c, B.cost64, io,
+                                 phase, s));
+      continue;
+    }
     const bool timed = reduce_timer && phase == 0;
     if (timed) DS3_TRY(timer_record(reduce_timer, true, s));
     DS3_TRY(launch_reduce_stream(dtype, 2, B.stream, B.seg_count, B.edges, B.items, tiles, B.xf, seg, B.partials,

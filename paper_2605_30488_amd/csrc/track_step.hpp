@@ -16,7 +16,8 @@ struct TrackState {
   double b[7];
   double E;       // E_track at T
   double lam;
-  int32_t trials, status, count, pad;
+  int32_t trials, status, count;
+  int32_t ticket;  // blocks of the current round that have stored their sums (k_track_round); 0 between rounds
 };
 static_assert(sizeof(TrackState) % sizeof(double) == 0, "copied as doubles");
 
@@ -124,8 +125,10 @@ constexpr int kStepTiles = 64;  // segment partials staged in LDS at a time
 // the block's threads side by side; one thread solves and moves the pose. Bound by that thread's chain of float64
 // operations: 10.8 us for a problem of 48 segments. Each thread loading its sums segment by segment, the cost in one
 // thread load by load, and the factor in scratch memory took 29 us.
-__device__ inline void track_step(const EdgeDev& E, int p, const float* __restrict__ partials,
-                                  const double* __restrict__ cost64, const TrackIo& io, int phase) {
+// SAME_LAUNCH: the sums were published by other blocks of this launch, so they are read at device scope.
+template <bool SAME_LAUNCH>
+__device__ inline void track_step(const EdgeDev& E, int p, const float* partials, const double* cost64,
+                                  const TrackIo& io, int phase) {
   __shared__ __align__(16) float stage[kStepTiles * kPartial];
   __shared__ double stage64[kStepTiles];
   __shared__ double S[37];
@@ -139,9 +142,28 @@ __device__ inline void track_step(const EdgeDev& E, int p, const float* __restri
   double s = 0.0, c = 0.0;
   for (int k0 = 0; k0 < E.n_tiles; k0 += kStepTiles) {
     const int m = min(kStepTiles, E.n_tiles - k0);
-    const float4* src = reinterpret_cast<const float4*>(partials + int64_t(E.tile0 + k0) * kPartial);
-    for (int q = t; q < m * (kPartial / 4); q += kStepThreads) reinterpret_cast<float4*>(stage)[q] = src[q];
-    if (t < m) stage64[t] = cost64[E.tile0 + k0 + t];
+    if constexpr (SAME_LAUNCH) {
+      // 8 B at a time, every load of the thread before its first use
+      const auto* src = reinterpret_cast<const unsigned long long*>(partials + int64_t(E.tile0 + k0) * kPartial);
+      constexpr int kLoads = kStepTiles * (kPartial / 2) / kStepThreads;
+      static_assert(kLoads * kStepThreads == kStepTiles * (kPartial / 2), "whole rounds of loads");
+      unsigned long long v[kLoads];
+      double c64 = 0.0;
+#pragma unroll
+      for (int u = 0; u < kLoads; ++u)
+        if (u * kStepThreads + t < m * (kPartial / 2))
+          v[u] = __hip_atomic_load(src + u * kStepThreads + t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (t < m) c64 = __hip_atomic_load(cost64 + E.tile0 + k0 + t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+      for (int u = 0; u < kLoads; ++u)
+        if (u * kStepThreads + t < m * (kPartial / 2))
+          reinterpret_cast<unsigned long long*>(stage)[u * kStepThreads + t] = v[u];
+      if (t < m) stage64[t] = c64;
+    } else {
+      const float4* src = reinterpret_cast<const float4*>(partials + int64_t(E.tile0 + k0) * kPartial);
+      for (int q = t; q < m * (kPartial / 4); q += kStepThreads) reinterpret_cast<float4*>(stage)[q] = src[q];
+      if (t < m) stage64[t] = cost64[E.tile0 + k0 + t];
+    }
     __syncthreads();
     if (t < 37) {
 #pragma unroll 8
@@ -176,6 +198,7 @@ __device__ inline void track_step(const EdgeDev& E, int p, const float* __restri
     if (t >= kWave && t < kWave + 8) st.T[t - kWave] = phase == 0 ? io.T_io[8 * int64_t(p) + t - kWave] : st.Tt[t - kWave];
   }
   if (t == 128) {
+    st.ticket = 0;
     if (phase == 0) {
       st.trials = 0;
       st.status = 0;
