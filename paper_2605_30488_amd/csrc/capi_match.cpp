@@ -59,99 +59,58 @@ static int upload(T* dst, const std::vector<T>& src, hipStream_t s) {
                    "hipMemcpyAsync(upload)");
 }
 
-// Deal entries with `tiles[k]` 256-px tiles into 8 bins (greedy, largest first) and lay the item map out:
-// `order` lists the entries bin by bin; prefix/bin_start/bin_tiles as in ItemMap. Returns the grid size.
-static int bin_items(const std::vector<int32_t>& tiles, std::vector<int32_t>& order,
-                     std::vector<int32_t>& prefix, std::vector<int32_t>& bin_start,
-                     std::vector<int32_t>& bin_tiles) {
-  const int n = int(tiles.size());
-  std::vector<int32_t> idx(n);
-  std::iota(idx.begin(), idx.end(), 0);
-  std::stable_sort(idx.begin(), idx.end(), [&](int a, int b) { return tiles[a] > tiles[b]; });
-  std::vector<std::vector<int32_t>> bins(8);
-  std::vector<int64_t> load(8, 0);
-  for (int k : idx) {
-    int b = int(std::min_element(load.begin(), load.end()) - load.begin());
-    bins[b].push_back(k);
-    load[b] += tiles[k];
-  }
-  order.clear();
-  prefix.clear();
-  bin_start.assign(9, 0);
-  bin_tiles.assign(8, 0);
-  int max_tiles = 0;
-  for (int b = 0; b < 8; ++b) {
-    bin_start[b] = int32_t(order.size());
-    int32_t acc = 0;
-    for (int k : bins[b]) {
-      order.push_back(k);
-      prefix.push_back(acc);
-      acc += tiles[k];
-    }
-    bin_tiles[b] = acc;
-    max_tiles = std::max(max_tiles, int(acc));
-  }
-  bin_start[8] = int32_t(order.size());
-  return 8 * max_tiles;
+// The item map of entries with items[k] items each.
+static ItemMap make_map(const std::vector<int32_t>& items, std::vector<int32_t>& prefix) {
+  prefix.assign(1, 0);
+  for (int32_t k : items) prefix.push_back(prefix.back() + k);
+  const int total = prefix.back();
+  return ItemMap{nullptr, int(items.size()), total, int((int64_t(total) + 7) / 8)};
 }
-
-struct ItemMapBufs {
-  int32_t *bin_start, *prefix, *bin_tiles;
-};
-
-static void carve_map(Carver& c, int n_entries, ItemMapBufs& m) {
-  m.bin_start = c.take<int32_t>(9);
-  m.prefix = c.take<int32_t>(std::max(n_entries, 1));
-  m.bin_tiles = c.take<int32_t>(8);
-}
-
-static ItemMap as_map(const ItemMapBufs& m) { return ItemMap{m.bin_start, m.prefix, m.bin_tiles}; }
 
 // Workspace of a batched match over `dirs` directions and `sides` mutual sides.
 struct MatchWs {
-  float4* rays;
+  float* rays;   // 3 per pixel
+  float* range;
   float* conf;
   int32_t* idx_tmp;
   MatchDir* dirs;
   MutualDir* md;
-  ItemMapBufs map_m, map_u;
-  unsigned* counts;
-  int64_t* npx;
+  int32_t *prefix_m, *prefix_u;
   unsigned* step_stripes;
   unsigned* part;   // per-tile mutual counts
-  int64_t* side;    // per count slot: first partial, number of partials
+  NuSide* nu_sides;
 };
 
 static size_t carve_match(void* base, int64_t ray_px, int64_t tmp_idx, int n_dirs, int n_sides, int n_edges,
                           MatchWs& W) {
   Carver c(base);
-  W.rays = c.take<float4>(size_t(std::max<int64_t>(ray_px, 1)));
+  W.rays = c.take<float>(size_t(std::max<int64_t>(ray_px, 1)) * 3);
+  W.range = c.take<float>(size_t(std::max<int64_t>(ray_px, 1)));
   W.conf = c.take<float>(size_t(std::max<int64_t>(ray_px, 1)));
   W.idx_tmp = c.take<int32_t>(size_t(std::max<int64_t>(tmp_idx, 1)));
   W.dirs = c.take<MatchDir>(std::max(n_dirs, 1));
   W.md = c.take<MutualDir>(std::max(n_sides, 1));
-  carve_map(c, n_dirs, W.map_m);
-  carve_map(c, n_sides, W.map_u);
-  W.counts = c.take<unsigned>(2 * size_t(std::max(n_edges, 1)));
-  W.npx = c.take<int64_t>(2 * size_t(std::max(n_edges, 1)));
+  W.prefix_m = c.take<int32_t>(size_t(n_dirs) + 1);
+  W.prefix_u = c.take<int32_t>(size_t(n_sides) + 1);
   W.step_stripes = c.take<unsigned>(size_t(kStepStripes) * kStripeStride);
   // every side has at most npx / 256 + 1 tiles and the sides' pixels add up to tmp_idx
   W.part = c.take<unsigned>(size_t(std::max<int64_t>(tmp_idx / 256 + n_sides + 1, 1)));
-  W.side = c.take<int64_t>(2 * size_t(std::max(n_sides, 1)));
+  W.nu_sides = c.take<NuSide>(std::max(n_sides, 1));
   return c.used;
 }
 
-// Per-tile partial slots of the sides (in their original order) and the per-slot table for the sums.
-static void assign_parts(std::vector<MutualDir>& sides, const std::vector<int32_t>& stiles,
-                         std::vector<int64_t>& side_tab) {
-  side_tab.assign(2 * sides.size(), 0);
+// Partial slots of the sides (one per block), in their order, and the table for their sums; returns the blocks of each.
+static std::vector<int32_t> assign_parts(MutualDir* sides, int n, int per, NuSide* tab) {
+  std::vector<int32_t> blocks;
   int64_t off = 0;
-  for (size_t k = 0; k < sides.size(); ++k) {
-    sides[k].part_off = off;
-    side_tab[2 * size_t(sides[k].count_slot)] = off;
-    side_tab[2 * size_t(sides[k].count_slot) + 1] = stiles[k];
-    off += stiles[k];
+  for (int k = 0; k < n; ++k) {
+    MutualDir& M = sides[k];
+    M.part_off = off;
+    blocks.push_back((mutual_runs(M.H_self, M.W_self) + per - 1) / per);
+    tab[M.count_slot] = NuSide{off, int64_t(M.H_self) * M.W_self, blocks.back(), 0};
+    off += blocks.back();
   }
+  return blocks;
 }
 
 // Shared driver: ray images, both directions of every edge, mutual check, nu.
@@ -170,57 +129,46 @@ static int run_match(const std::vector<EdgeSpec>& es, const void* cross, ds3_dty
                      int32_t* admit, uint64_t* lm_steps, ds3_timer* timer, hipStream_t s) {
   const int ne = int(es.size());
   std::vector<MatchDir> dirs;
-  std::vector<int32_t> dtiles;
   std::vector<MutualDir> sides;
-  std::vector<int32_t> stiles;
-  std::vector<int64_t> npx;
+  bool big = false;
+  int64_t strips = 0, runs = 0;
   for (int e = 0; e < ne; ++e) {
     const EdgeSpec& E = es[e];
-    MatchDir a{E.ray_i, E.q_ji, E.tmp_ji, E.Hi, E.Wi, E.Hj, E.Wj};   // queries: pixels of j
-    MatchDir b{E.ray_j, E.q_ij, E.tmp_ij, E.Hj, E.Wj, E.Hi, E.Wi};   // queries: pixels of i
-    dirs.push_back(a);
-    dtiles.push_back(match_tiles(E.Hj, E.Wj));
-    dirs.push_back(b);
-    dtiles.push_back(match_tiles(E.Hi, E.Wi));
-    MutualDir sj{E.tmp_ji, E.tmp_ij, E.out_off, W.conf + E.ray_j, W.conf + E.ray_i, E.Hj, E.Wj, E.Hi, E.Wi,
-                 2 * e + 1, 1};
-    MutualDir si{E.tmp_ij, E.tmp_ji, 0, W.conf + E.ray_i, W.conf + E.ray_j, E.Hi, E.Wi, E.Hj, E.Wj, 2 * e, 0};
-    sides.push_back(sj);
-    stiles.push_back(int32_t((int64_t(E.Hj) * E.Wj + kMutualPx - 1) / kMutualPx));
-    sides.push_back(si);
-    stiles.push_back(int32_t((int64_t(E.Hi) * E.Wi + kMutualPx - 1) / kMutualPx));
-    npx.push_back(int64_t(E.Hi) * E.Wi);
-    npx.push_back(int64_t(E.Hj) * E.Wj);
+    dirs.push_back(MatchDir{E.ray_i, E.q_ji, E.tmp_ji, E.Hi, E.Wi, E.Hj, E.Wj});  // queries: pixels of j
+    dirs.push_back(MatchDir{E.ray_j, E.q_ij, E.tmp_ij, E.Hj, E.Wj, E.Hi, E.Wi});  // queries: pixels of i
+    strips += match_strips(E.Hj, E.Wj) + match_strips(E.Hi, E.Wi);
+    big = big || match_big(E.Hi, E.Wi) || match_big(E.Hj, E.Wj);
+    // an edge's sides read the same matches and confidences: they follow each other
+    sides.push_back(MutualDir{E.tmp_ji, E.tmp_ij, E.out_off, W.conf + E.ray_j, W.conf + E.ray_i, E.Hj, E.Wj, E.Hi, E.Wi,
+                              2 * e + 1, 1});
+    sides.push_back(MutualDir{E.tmp_ij, E.tmp_ji, 0, W.conf + E.ray_i, W.conf + E.ray_j, E.Hi, E.Wi, E.Hj, E.Wj, 2 * e,
+                              0});
+    runs += mutual_runs(E.Hj, E.Wj) + mutual_runs(E.Hi, E.Wi);
   }
-  std::vector<int32_t> order, prefix, bs, bt;
-  const int grid_m = bin_items(dtiles, order, prefix, bs, bt);
-  std::vector<MatchDir> dirs_o;
-  for (int k : order) dirs_o.push_back(dirs[k]);
-  DS3_TRY(upload(W.dirs, dirs_o, s));
-  DS3_TRY(upload(W.map_m.bin_start, bs, s));
-  DS3_TRY(upload(W.map_m.prefix, prefix, s));
-  DS3_TRY(upload(W.map_m.bin_tiles, bt, s));
-  std::vector<int64_t> side_tab;
-  assign_parts(sides, stiles, side_tab);
-  DS3_TRY(upload(W.side, side_tab, s));
-  std::vector<int32_t> order2, prefix2, bs2, bt2;
-  const int grid_u = bin_items(stiles, order2, prefix2, bs2, bt2);
-  std::vector<MutualDir> sides_o;
-  for (int k : order2) sides_o.push_back(sides[k]);
-  DS3_TRY(upload(W.md, sides_o, s));
-  DS3_TRY(upload(W.map_u.bin_start, bs2, s));
-  DS3_TRY(upload(W.map_u.prefix, prefix2, s));
-  DS3_TRY(upload(W.map_u.bin_tiles, bt2, s));
-  DS3_TRY(upload(W.npx, npx, s));
+  // directions with the same reference follow each other
+  std::stable_sort(dirs.begin(), dirs.end(), [](const MatchDir& a, const MatchDir& b) { return a.ref_off < b.ref_off; });
+  const int per = match_per(strips);
+  std::vector<int32_t> units, prefix, prefix_u;
+  for (const MatchDir& D : dirs) units.push_back((match_strips(D.Hq, D.Wq) + per - 1) / per);
+  const int per_u = mutual_per(runs);
+  std::vector<NuSide> nu_sides(sides.size());
+  ItemMap map_m = make_map(units, prefix);
+  ItemMap map_u = make_map(assign_parts(sides.data(), int(sides.size()), per_u, nu_sides.data()), prefix_u);
+  map_m.prefix = W.prefix_m;
+  map_u.prefix = W.prefix_u;
+  DS3_TRY(upload(W.dirs, dirs, s));
+  DS3_TRY(upload(W.prefix_m, prefix, s));
+  DS3_TRY(upload(W.md, sides, s));
+  DS3_TRY(upload(W.prefix_u, prefix_u, s));
+  DS3_TRY(upload(W.nu_sides, nu_sides, s));
   unsigned* stripes = lm_steps ? W.step_stripes : nullptr;
   if (stripes) DS3_TRY(launch_fill_u32(stripes, size_t(kStepStripes) * kStripeStride, 0u, s));
   DS3_TRY(timer_record(timer, true, s));
-  DS3_TRY(launch_match_batched(W.rays, cross, dt, W.dirs, as_map(W.map_m), grid_m, C, W.idx_tmp, stripes, s));
+  DS3_TRY(launch_match_batched(W.rays, W.range, cross, dt, big, W.dirs, map_m, per, C, W.idx_tmp, stripes, s));
   DS3_TRY(timer_record(timer, false, s));
   if (stripes) DS3_TRY(launch_sum_stripes(stripes, reinterpret_cast<unsigned long long*>(lm_steps), s));
-  DS3_TRY(launch_mutual(W.md, as_map(W.map_u), grid_u, dt, C, W.idx_tmp, idx_out, valid_out, W.part, s));
-  DS3_TRY(launch_side_counts(W.part, W.side, 2 * ne, W.counts, s));
-  return launch_nu_finalize(W.counts, W.npx, ne, nu_min, nu, admit, s);
+  DS3_TRY(launch_mutual(W.md, map_u, per_u, C, W.idx_tmp, idx_out, valid_out, W.part, s));
+  return launch_nu(W.part, W.nu_sides, ne, nu_min, nu, admit, s);
 }
 
 static int check_arch_local() {
@@ -242,7 +190,7 @@ extern "C" {
 size_t ds3_match_workspace_bytes(int32_t H_ref, int32_t W_ref) {
   if (H_ref <= 0 || W_ref <= 0) return 0;
   Carver c(nullptr);
-  c.take<float4>(size_t(H_ref) * W_ref);
+  c.take<float4>(size_t(H_ref) * W_ref);  // rays and ranges
   return c.used;
 }
 
@@ -262,10 +210,11 @@ int ds3_match(const void* ref_xyzc, ds3_image ref, const void* qry_xyzc, ds3_ima
   const int pxb = dtype == DS3_F32 ? 16 : 8;
   const char* rp = static_cast<const char*>(ref_xyzc) + ref.px_offset * pxb;
   const char* qp = static_cast<const char*>(qry_xyzc) + qry.px_offset * pxb;
-  float4* rays = static_cast<float4*>(workspace);
-  DS3_TRY(launch_raymap(rp, int64_t(ref.H) * ref.W, dtype, rays, nullptr, s));
-  return launch_match_one(rays, ref.H, ref.W, qp, qry.H, qry.W, dtype, make_match_const(*params), idx_out,
-                          p_out, iters_out, s);
+  float* rays = static_cast<float*>(workspace);
+  float* range = rays + 3 * int64_t(ref.H) * ref.W;  // the workspace holds four floats per pixel
+  DS3_TRY(launch_raymap(rp, int64_t(ref.H) * ref.W, nullptr, 0, dtype, rays, range, nullptr, s));
+  const MatchFew F{{MatchOne{rays, range, qp, idx_out, p_out, iters_out, ref.H, ref.W, qry.H, qry.W}, MatchOne{}}, 0};
+  return launch_match_few(F, 1, dtype, make_match_const(*params), s);
 }
 
 size_t ds3_match_bidir_workspace_bytes(int32_t H_i, int32_t W_i, int32_t H_j, int32_t W_j) {
@@ -298,35 +247,22 @@ int ds3_match_bidir(const void* X_ii, const void* X_ji, const void* X_jj, const 
   auto at = [&](const void* p, int64_t off) { return static_cast<const char*>(p) + off * pxb; };
   const void* ii = at(X_ii, img_i.px_offset);
   const void* jj = at(X_jj, img_j.px_offset);
-  DS3_TRY(launch_raymap(ii, ni, dtype, W.rays, W.conf, s));
-  DS3_TRY(launch_raymap(jj, nj, dtype, W.rays + ni, W.conf + ni, s));
-  // the two cross-view maps live in different buffers: run the two directions as single launches and
-  // reuse the batched mutual kernel over both sides
+  DS3_TRY(launch_raymap(ii, ni, jj, nj, dtype, W.rays, W.range, W.conf, s));
+  // every table of one edge is a kernel argument
   const MatchConst C = make_match_const(*params);
-  DS3_TRY(launch_match_one(W.rays, img_i.H, img_i.W, at(X_ji, img_j.px_offset), img_j.H, img_j.W, dtype, C,
-                           W.idx_tmp, nullptr, nullptr, s));
-  DS3_TRY(launch_match_one(W.rays + ni, img_j.H, img_j.W, at(X_ij, img_i.px_offset), img_i.H, img_i.W,
-                           dtype, C, W.idx_tmp + nj, nullptr, nullptr, s));
-  std::vector<MutualDir> sides = {
-      MutualDir{0, nj, 0, W.conf + ni, W.conf, img_j.H, img_j.W, img_i.H, img_i.W, 1, 1},
-      MutualDir{nj, 0, 0, W.conf, W.conf + ni, img_i.H, img_i.W, img_j.H, img_j.W, 0, 0}};
-  std::vector<int32_t> stiles = {int32_t((nj + kMutualPx - 1) / kMutualPx), int32_t((ni + kMutualPx - 1) / kMutualPx)};
-  std::vector<int64_t> side_tab;
-  assign_parts(sides, stiles, side_tab);
-  DS3_TRY(upload(W.side, side_tab, s));
-  std::vector<int32_t> order, prefix, bs, bt;
-  const int grid = bin_items(stiles, order, prefix, bs, bt);
-  std::vector<MutualDir> sides_o;
-  for (int k : order) sides_o.push_back(sides[k]);
-  DS3_TRY(upload(W.md, sides_o, s));
-  DS3_TRY(upload(W.map_u.bin_start, bs, s));
-  DS3_TRY(upload(W.map_u.prefix, prefix, s));
-  DS3_TRY(upload(W.map_u.bin_tiles, bt, s));
-  std::vector<int64_t> npx = {ni, nj};
-  DS3_TRY(upload(W.npx, npx, s));
-  DS3_TRY(launch_mutual(W.md, as_map(W.map_u), grid, dtype, C, W.idx_tmp, idx_j2i, valid_j, W.part, s));
-  DS3_TRY(launch_side_counts(W.part, W.side, 2, W.counts, s));
-  return launch_nu_finalize(W.counts, W.npx, 1, params->nu_min, nu, admit, s);
+  const MatchFew F{{MatchOne{W.rays, W.range, at(X_ji, img_j.px_offset), W.idx_tmp, nullptr, nullptr, img_i.H, img_i.W,
+                             img_j.H, img_j.W},
+                    MatchOne{W.rays + 3 * ni, W.range + ni, at(X_ij, img_i.px_offset), W.idx_tmp + nj, nullptr, nullptr,
+                             img_j.H, img_j.W, img_i.H, img_i.W}},
+                   0};
+  DS3_TRY(launch_match_few(F, 2, dtype, C, s));
+  MutualPair M{{MutualDir{0, nj, 0, W.conf + ni, W.conf, img_j.H, img_j.W, img_i.H, img_i.W, 1, 1},
+                MutualDir{nj, 0, 0, W.conf, W.conf + ni, img_i.H, img_i.W, img_j.H, img_j.W, 0, 0}},
+               mutual_runs(img_j.H, img_j.W)};
+  NuSide nu_sides[2];
+  assign_parts(M.d, 2, 1, nu_sides);
+  DS3_TRY(launch_mutual_pair(M, M.tiles0 + mutual_runs(img_i.H, img_i.W), C, W.idx_tmp, idx_j2i, valid_j, W.part, s));
+  return launch_nu_pair(W.part, nu_sides[0], nu_sides[1], params->nu_min, nu, admit, s);
 }
 
 size_t ds3_match_batch_workspace_bytes(int32_t n_kf, const ds3_image* kf, int32_t n_edges,
@@ -384,7 +320,7 @@ int ds3_match_batch(const void* kf_arena, const ds3_image* kf, int32_t n_kf, con
   }
   MatchWs W;
   carve_match(workspace, ray_px, tmp, 2 * n_edges, 2 * n_edges, n_edges, W);
-  DS3_TRY(launch_raymap(kf_arena, ray_px, dtype, W.rays, W.conf, s));
+  DS3_TRY(launch_raymap(kf_arena, ray_px, nullptr, 0, dtype, W.rays, W.range, W.conf, s));
   return run_match(es, cross_arena, dtype, make_match_const(*params), params->nu_min, W, idx_arena,
                    valid_arena, nu, admit, lm_steps, match_timer, s);
 }
