@@ -269,24 +269,22 @@ static int edge_cal_table(const ds3_gn_params& p, const Topology& T, std::vector
   return make_edge_cal(p.K, T.n_kf, T.kf_w.data(), T.edges.data(), T.n_edges, out.data());
 }
 
-// Plain-form linearisation: prep, one residual launch per edge, finalize, assembly, cost sum.
+// Plain-form linearisation: prep (with H cleared), one residual launch per edge, finalize, assembly (which clears the dense
+// solver's first synchronisation words).
 static int gn_linearize_plain(const double* poses, const Topology& T, const GnBuffers& B,
                               const void* arena, ds3_dtype dt, const int32_t* idx,
-                              const ds3_gn_params& p, double* H, double* g, double* cost_out,
-                              int64_t* count_out, hipStream_t s) {
+                              const ds3_gn_params& p, double* H, double* g, hipStream_t s) {
   const GnConst c = make_gn_const(p);
   std::vector<EdgeCal> cal;
   DS3_TRY(edge_cal_table(p, T, cal));
-  DS3_TRY(launch_gn_prep(poses, B.edges, T.n_edges, B.xf, B.Ad, s));
+  const size_t n = 7 * size_t(T.n_kf);
+  DS3_TRY(launch_gn_prep(poses, B.edges, T.n_edges, B.xf, B.Ad, s, H, n * n));
   for (int e = 0; e < T.n_edges; ++e)
     DS3_TRY(launch_edge_reduce_one(dt, kPlainPPT, arena, T.edges[e], e, B.xf, idx, B.partials, c, s,
                                    p.K ? &cal[e] : nullptr));
   DS3_TRY(launch_edge_finalize(B.edges, T.n_edges, B.partials, B.Ad, B.A_e, B.b_e, B.cost_e, B.count_e, s));
-  const size_t n = 7 * size_t(T.n_kf);
-  DS3_TRY(launch_fill(H, n * n, 0.0, s));
-  DS3_TRY(launch_assemble(T.n_kf, B.node_ptr, B.node_adj, B.pair_ptr, B.pair_edges, B.pair_ij, T.n_pairs,
-                          B.A_e, B.b_e, B.anchor, H, g, s));
-  return launch_sum_costs(B.cost_e, B.count_e, T.n_edges, cost_out, count_out, s);
+  return launch_assemble(T.n_kf, B.node_ptr, B.node_adj, B.pair_ptr, B.pair_edges, B.pair_ij, T.n_pairs,
+                         B.A_e, B.b_e, B.anchor, H, g, s, chol_sync_words(B.chol_ws, int(n)), 4);
 }
 
 }  // namespace ds3
@@ -411,7 +409,8 @@ int ds3_gn_linearize(const double* poses, int32_t n_kf, const ds3_image* kf, con
   DS3_TRY(check_arch());
   hipStream_t s = S(stream);
   DS3_TRY(upload_topology(T, B, s));
-  return gn_linearize_plain(poses, T, B, arena, dtype, idx, *params, H, g, cost_out, count_out, s);
+  DS3_TRY(gn_linearize_plain(poses, T, B, arena, dtype, idx, *params, H, g, s));
+  return launch_sum_costs(B.cost_e, B.count_e, T.n_edges, cost_out, count_out, s);
 }
 
 int ds3_sim3_gn_step(double* poses, int32_t n_kf, const ds3_image* kf, const void* arena, ds3_dtype dtype,
@@ -429,12 +428,14 @@ int ds3_sim3_gn_step(double* poses, int32_t n_kf, const ds3_image* kf, const voi
   DS3_TRY(check_arch());
   hipStream_t s = S(stream);
   DS3_TRY(upload_topology(T, B, s));
-  DS3_TRY(gn_linearize_plain(poses, T, B, arena, dtype, idx, *params, B.H, B.g, cost_out, nullptr, s));
+  DS3_TRY(gn_linearize_plain(poses, T, B, arena, dtype, idx, *params, B.H, B.g, s));
   const int n = 7 * n_kf;
   double* tau = tau_out ? tau_out : B.tau;
   DS3_TRY(launch_chol_ladder(B.H, B.g, n, params->lambda, params->eps0, params->eps_mult,
-                             params->max_attempts, tau, status_out, B.chol_ws, s));
-  return launch_sim3_update(poses, tau, B.anchor, n_kf, s);
+                             params->max_attempts, tau, status_out, B.chol_ws, s, false, true));
+  const StepTail tail{poses, tau, B.anchor, n_kf, B.cost_e, B.count_e, n_edges, cost_out};
+  return launch_step_tail(B.H, B.g, n, params->lambda, params->eps0, params->eps_mult, params->max_attempts, tau,
+                          status_out, B.chol_ws, tail, s);
 }
 
 int ds3_gn_cost(const double* poses, int32_t n_kf, const ds3_image* kf, const void* arena, ds3_dtype dtype,
@@ -537,9 +538,9 @@ static int plan_iteration(Plan& P, hipStream_t s, bool timed) {
                                P.B.count_e, s));
   const size_t n = 7 * size_t(P.T.n_kf);
   // H was cleared once at plan creation: the assembly rewrites every block of its fixed nonzero pattern
-  // with the tile-sparse solver, the assembly also clears the solve's barrier words and attempt-0 flag (one
-  // launch fewer per iteration)
-  unsigned* sync = P.tc ? chol_sync_words(P.B.chol_ws, int(n)) : nullptr;
+  // with the tile-sparse and the dense solver, the assembly also clears the solve's barrier words and attempt-0 flag
+  // (one launch fewer per iteration)
+  unsigned* sync = P.sp ? nullptr : chol_sync_words(P.B.chol_ws, int(n));
   DS3_TRY(launch_assemble(P.T.n_kf, P.B.node_ptr, P.B.node_adj, P.B.pair_ptr, P.B.pair_edges, P.B.pair_ij,
                           P.T.n_pairs, P.B.A_e, P.B.b_e, P.B.anchor, P.B.H, P.B.g, s, sync, sync ? 4 : 0));
   int32_t* status = reinterpret_cast<int32_t*>(P.B.counter + 8);
@@ -551,7 +552,7 @@ static int plan_iteration(Plan& P, hipStream_t s, bool timed) {
                             status, P.B.chol_ws, s, true));
   else
     DS3_TRY(launch_chol_ladder(P.B.H, P.B.g, int(n), P.p.lambda, P.p.eps0, P.p.eps_mult, P.p.max_attempts,
-                               P.B.tau, status, P.B.chol_ws, s));
+                               P.B.tau, status, P.B.chol_ws, s, true, true));
   // the update, and the cost at the iteration's input poses (cost_e is rewritten only by the next iteration)
   // with the ladder status to the history, in one launch
   return launch_update_record(P.poses, P.B.tau, P.B.anchor, P.T.n_kf, P.B.cost_e, P.B.count_e, P.T.n_edges,

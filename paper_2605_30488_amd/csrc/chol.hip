@@ -16,7 +16,10 @@
 // own bounded grid barriers (the common case never pays for the ladder).
 //
 // Tile products run on the float64 MFMA; LDS tiles use row stride NB + 2.
+#include <algorithm>
+
 #include "chol_tile.hpp"
+#include "gn_tail.hpp"
 #include "internal.hpp"
 
 namespace ds3 {
@@ -388,8 +391,8 @@ __device__ bool grid_barrier(unsigned* sync, unsigned nblocks) {
   return s_ok != 0;
 }
 
-__global__ __launch_bounds__(kCholThreads) void k_chol_fallback(CholArgs a) {
-  if (a.sync[3] == 0u) return;  // attempt 0 succeeded (uniform)
+// Attempts 1.. by every block of the grid.
+__device__ void chol_fallback(const CholArgs& a) {
   __shared__ double S0[NB * LDT];
   __shared__ double S1[NB * LDT];
   __shared__ double S2[NB * LDT];
@@ -494,6 +497,22 @@ __global__ __launch_bounds__(kCholThreads) void k_chol_fallback(CholArgs a) {
   }
 }
 
+__global__ __launch_bounds__(kCholThreads) void k_chol_fallback(CholArgs a) {
+  if (a.sync[3] == 0u) return;  // attempt 0 succeeded (uniform)
+  chol_fallback(a);
+}
+
+// The end of a plain step: the fallback when attempt 0 failed, and after it the poses and the cost. (In a plan's graph the
+// same fusion, with the next edges' preparation as well, was slower than the three launches: 95 against 91 us per
+// iteration of 50 keyframes, its chain of float64 operations being longer than the launches.)
+__global__ __launch_bounds__(kCholThreads) void k_step_tail(CholArgs a, StepTail t) {
+  if (a.attempts > 1 && a.sync[3] != 0u) {  // uniform
+    chol_fallback(a);
+    grid_barrier(a.sync, gridDim.x);  // tau and the status are written; on a reported error nothing waits
+  }
+  step_tail(t);
+}
+
 static void chol_dims(int n, int& nt, int& np) {
   nt = (n + NB - 1) / NB;
   if (nt < 1) nt = 1;
@@ -553,12 +572,25 @@ unsigned* chol_sync_words(void* ws, int n) {
   return c.take<unsigned>(4 + (kMaxAttempts + 1) * nt);
 }
 
-static int launch_fallback(const CholArgs& a, hipStream_t s) {
+static int fallback_blocks(const CholArgs& a) {
   int G = (a.nt - 1) * a.nt / 2;
   if (G < 1) G = 1;
   if (G > 128) G = 128;
-  hipLaunchKernelGGL(k_chol_fallback, dim3(G), dim3(kCholThreads), 0, s, a);
+  return G;
+}
+
+static int launch_fallback(const CholArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL(k_chol_fallback, dim3(fallback_blocks(a)), dim3(kCholThreads), 0, s, a);
   return check_hip(hipGetLastError(), "k_chol_fallback");
+}
+
+int launch_step_tail(const double* H, const double* g, int n, double lambda, double eps0, double mult, int attempts,
+                     double* tau, int32_t* status, void* ws, const StepTail& t, hipStream_t s) {
+  CholArgs a;
+  DS3_TRY(chol_args(a, H, g, n, lambda, eps0, mult, attempts, tau, status, ws));
+  const int blocks = std::max(2, fallback_blocks(a));  // all resident at once, as the fallback's barriers need
+  hipLaunchKernelGGL(k_step_tail, dim3(blocks), dim3(kCholThreads), 0, s, a, t);
+  return check_hip(hipGetLastError(), "k_step_tail");
 }
 
 int launch_chol_fallback(const double* H, const double* g, int n, double lambda, double eps0, double mult,
@@ -569,11 +601,12 @@ int launch_chol_fallback(const double* H, const double* g, int n, double lambda,
 }
 
 int launch_chol_ladder(const double* H, const double* g, int n, double lambda, double eps0, double mult,
-                       int attempts, double* tau, int32_t* status, void* ws, hipStream_t s) {
+                       int attempts, double* tau, int32_t* status, void* ws, hipStream_t s, bool fallback,
+                       bool sync_cleared) {
   CholArgs a;
   DS3_TRY(chol_args(a, H, g, n, lambda, eps0, mult, attempts, tau, status, ws));
   // barrier words start at zero (a fill kernel, not a memset, so the sequence can be captured)
-  DS3_TRY(launch_fill_u32(a.sync, 3, 0u, s));
+  if (!sync_cleared) DS3_TRY(launch_fill_u32(a.sync, 3, 0u, s));
   hipLaunchKernelGGL(k_chol_init, dim3(blocks_for_tiles(a.nt * (a.nt + 1) / 2)), dim3(kCholThreads), 0, s, a);
   DS3_TRY(check_hip(hipGetLastError(), "k_chol_init"));
   for (int k = 0; k + 1 < a.nt; ++k) {
@@ -582,7 +615,7 @@ int launch_chol_ladder(const double* H, const double* g, int n, double lambda, d
     DS3_TRY(check_hip(hipGetLastError(), "k_chol_panel"));
   }
   DS3_TRY(launch_backsub(a, s));
-  if (attempts > 1) DS3_TRY(launch_fallback(a, s));
+  if (attempts > 1 && fallback) DS3_TRY(launch_fallback(a, s));
   return DS3_OK;
 }
 

@@ -22,6 +22,7 @@
 #include <string>
 
 #include "common.hpp"
+#include "gn_tail.hpp"
 #include "internal.hpp"
 #include "sim3.hpp"
 #include "track_step.hpp"
@@ -50,8 +51,10 @@ GnConst make_gn_const(const ds3_gn_params& p) {
 // Pose prep: T_ij = T_i^-1 T_j (float32 copy for the residual kernel) and Ad_{T_i^-1} (float64).
 // --------------------------------------------------------------------------------------------------
 __global__ void k_gn_prep(const double* __restrict__ poses, const EdgeDev* __restrict__ edges,
-                          int n_edges, EdgeXf* __restrict__ xf, double* __restrict__ Ad) {
+                          int n_edges, EdgeXf* __restrict__ xf, double* __restrict__ Ad, double* __restrict__ zero,
+                          size_t n_zero) {
   int e = blockIdx.x * blockDim.x + threadIdx.x;
+  for (size_t k = e; k < n_zero; k += size_t(gridDim.x) * blockDim.x) zero[k] = 0.0;
   if (e >= n_edges) return;
   const EdgeDev E = edges[e];
   Sim3 Ti = sim3_load(poses + 8 * E.i);
@@ -71,11 +74,11 @@ __global__ void k_gn_prep(const double* __restrict__ poses, const EdgeDev* __res
 }
 
 int launch_gn_prep(const double* poses, const EdgeDev* edges, int n_edges, EdgeXf* xf, double* Ad,
-                   hipStream_t s) {
+                   hipStream_t s, double* zero, size_t n_zero) {
   int threads = 128;
-  int blocks = (n_edges + threads - 1) / threads;
+  int blocks = std::max((n_edges + threads - 1) / threads, int(std::min<size_t>((n_zero + 1023) / 1024, 2048)));
   if (blocks < 1) blocks = 1;
-  hipLaunchKernelGGL(k_gn_prep, dim3(blocks), dim3(threads), 0, s, poses, edges, n_edges, xf, Ad);
+  hipLaunchKernelGGL(k_gn_prep, dim3(blocks), dim3(threads), 0, s, poses, edges, n_edges, xf, Ad, zero, n_zero);
   return check_hip(hipGetLastError(), "k_gn_prep");
 }
 
@@ -1206,46 +1209,6 @@ int launch_assemble(int n_kf, const int32_t* node_ptr, const int32_t* node_adj, 
   hipLaunchKernelGGL(k_assemble, dim3(n_kf + n_pairs), dim3(64), 0, s, n_kf, node_ptr, node_adj, pair_ptr,
                      pair_edges, pair_ij, A_e, b_e, anchor_mask, H, g, zero, n_zero);
   return check_hip(hipGetLastError(), "k_assemble");
-}
-
-// Deterministic sum of per-edge costs and counts over one block of 256 threads (fixed strided split + fixed
-// tree); thread 0 writes them. With ctr, the sum and *status are also appended to a history (slot *ctr,
-// then ctr advances; slots past hist_len are dropped).
-__device__ inline void sum_costs_block(const double* __restrict__ cost_e, const int64_t* __restrict__ count_e,
-                                       int n_edges, double* __restrict__ cost_out, int64_t* __restrict__ count_out,
-                                       const int32_t* __restrict__ status, unsigned* __restrict__ ctr,
-                                       double* __restrict__ cost_hist, int32_t* __restrict__ status_hist,
-                                       int hist_len) {
-  __shared__ double sc[256];
-  __shared__ long long sn[256];
-  double c = 0.0;
-  long long m = 0;
-  for (int e = threadIdx.x; e < n_edges; e += 256) {
-    c += cost_e[e];
-    m += count_e[e];
-  }
-  sc[threadIdx.x] = c;
-  sn[threadIdx.x] = m;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (int(threadIdx.x) < w) {
-      sc[threadIdx.x] += sc[threadIdx.x + w];
-      sn[threadIdx.x] += sn[threadIdx.x + w];
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    if (cost_out) *cost_out = sc[0];
-    if (count_out) *count_out = sn[0];
-    if (ctr) {
-      const unsigned k = *ctr;
-      if (k < unsigned(hist_len)) {
-        cost_hist[k] = sc[0];
-        status_hist[k] = *status;
-      }
-      *ctr = k + 1;
-    }
-  }
 }
 
 __global__ __launch_bounds__(256) void k_sum_costs(const double* __restrict__ cost_e,

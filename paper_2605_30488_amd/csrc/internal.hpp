@@ -111,7 +111,7 @@ struct TrackConst {
 
 // gn.hip
 int launch_gn_prep(const double* poses, const EdgeDev* edges, int n_edges, EdgeXf* xf, double* Ad,
-                   hipStream_t s);
+                   hipStream_t s, double* zero = nullptr, size_t n_zero = 0);  // also clears zero[0 .. n_zero)
 int launch_edge_reduce_one(ds3_dtype dt, int ppt, const void* arena, const EdgeDev& e, int edge_id,
                            const EdgeXf* xf, const int32_t* idx_arena, float* partials, GnConst c,
                            hipStream_t s, const EdgeCal* cal = nullptr);
@@ -145,6 +145,17 @@ int launch_update_record(double* poses, const double* tau, const uint8_t* fixed,
                          const int64_t* count_e, int n_edges, double* cost_out, int64_t* count_out,
                          const int32_t* status, unsigned* ctr, double* cost_hist, int32_t* status_hist, int hist_len,
                          hipStream_t s);
+// What the launch that ends a plain step does after the solve (step_tail).
+struct StepTail {
+  double* poses;
+  const double* tau;
+  const uint8_t* fixed;  // may be NULL
+  int n_kf;
+  const double* cost_e;
+  const int64_t* count_e;
+  int n_edges;
+  double* cost_out;
+};
 int launch_fill(double* p, size_t n, double v, hipStream_t s);
 int launch_fill_u32(unsigned* p, size_t n, unsigned v, hipStream_t s);
 int launch_copy_f64(const double* src, double* dst, size_t n, hipStream_t s);
@@ -159,14 +170,20 @@ int launch_track_step(const EdgeDev* edges, int n, const float* partials, const 
 
 // chol.hip
 size_t chol_workspace_bytes(int n);
+// fallback: attempts 1.. run in the call when attempt 0 fails (else the caller's launch_step_tail runs them);
+// sync_cleared: the first four words of chol_sync_words were already cleared on stream s
 int launch_chol_ladder(const double* H, const double* g, int n, double lambda, double eps0, double mult,
-                       int attempts, double* tau, int32_t* status, void* ws, hipStream_t s);
+                       int attempts, double* tau, int32_t* status, void* ws, hipStream_t s, bool fallback = true,
+                       bool sync_cleared = false);
 
 // the dense workspace's synchronisation words ([2] error, [3] attempt 0 failed) and its persistent
 // fallback alone (attempts 1.., run only when attempt 0 failed)
 unsigned* chol_sync_words(void* ws, int n);
 int launch_chol_fallback(const double* H, const double* g, int n, double lambda, double eps0, double mult,
                          int attempts, double* tau, int32_t* status, void* ws, hipStream_t s);
+// the end of a plain step in one launch: that fallback, then t
+int launch_step_tail(const double* H, const double* g, int n, double lambda, double eps0, double mult, int attempts,
+                     double* tau, int32_t* status, void* ws, const StepTail& t, hipStream_t s);
 
 // spchol.hip: block-sparse ladder solve for a fixed keyframe-pair pattern, and the minimum-degree order
 // both sparse solvers start from
