@@ -5,6 +5,7 @@
 #include <sys/types.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cerrno>
 #include <chrono>
 #include <cmath>
@@ -49,13 +50,17 @@ int device_cu_count() {
   return cus;
 }
 
-static int check_arch() {
+int check_arch() {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return fail(DS3_EHIP, "no HIP device");
+  // what a device is does not change, and reading its properties takes longer than a launch: one bit per device
+  static std::atomic<uint64_t> known{0};
+  if (dev < 64 && (known.load(std::memory_order_relaxed) >> dev & 1)) return DS3_OK;
   hipDeviceProp_t prop;
   if (hipGetDeviceProperties(&prop, dev) != hipSuccess) return fail(DS3_EHIP, "hipGetDeviceProperties");
   if (std::strncmp(prop.gcnArchName, "gfx950", 6) != 0)
     return fail(DS3_ENOTSUP, std::string("libds3 is built for gfx950, device is ") + prop.gcnArchName);
+  if (dev < 64) known.fetch_or(uint64_t(1) << dev, std::memory_order_relaxed);
   return DS3_OK;
 }
 
@@ -202,14 +207,8 @@ static size_t carve_gn(void* base, const Topology& T, GnBuffers& B) {
   Carver c(base);
   const int E = std::max(T.n_edges, 1);
   const size_t n = 7 * size_t(T.n_kf);
+  // the tables of upload_topology, in its order
   B.edges = c.take<EdgeDev>(E);
-  B.xf = c.take<EdgeXf>(E);
-  B.Ad = c.take<double>(49 * size_t(E));
-  B.partials = c.take<float>(size_t(std::max(T.total_tiles, 1)) * kPartial);
-  B.A_e = c.take<double>(49 * size_t(E));
-  B.b_e = c.take<double>(7 * size_t(E));
-  B.cost_e = c.take<double>(E);
-  B.count_e = c.take<int64_t>(E);
   B.kf_off = c.take<int64_t>(T.n_kf);
   B.kf_npx = c.take<int32_t>(T.n_kf);
   B.node_ptr = c.take<int32_t>(T.n_kf + 1);
@@ -218,6 +217,13 @@ static size_t carve_gn(void* base, const Topology& T, GnBuffers& B) {
   B.pair_edges = c.take<int32_t>(E);
   B.pair_ij = c.take<int32_t>(2 * size_t(E));
   B.anchor = c.take<uint8_t>(T.n_kf);
+  B.xf = c.take<EdgeXf>(E);
+  B.Ad = c.take<double>(49 * size_t(E));
+  B.partials = c.take<float>(size_t(std::max(T.total_tiles, 1)) * kPartial);
+  B.A_e = c.take<double>(49 * size_t(E));
+  B.b_e = c.take<double>(7 * size_t(E));
+  B.cost_e = c.take<double>(E);
+  B.count_e = c.take<int64_t>(E);
   B.H = c.take<double>(n * n);
   B.g = c.take<double>(n);
   B.tau = c.take<double>(n);
@@ -230,16 +236,17 @@ static size_t carve_gn(void* base, const Topology& T, GnBuffers& B) {
 }
 
 static int upload_topology(const Topology& T, GnBuffers& B, hipStream_t s) {
-  DS3_TRY(upload(B.edges, T.edges, s));
-  DS3_TRY(upload(B.kf_off, T.kf_off, s));
-  DS3_TRY(upload(B.kf_npx, T.kf_npx, s));
-  DS3_TRY(upload(B.node_ptr, T.node_ptr, s));
-  DS3_TRY(upload(B.node_adj, T.node_adj, s));
-  DS3_TRY(upload(B.pair_ptr, T.pair_ptr, s));
-  DS3_TRY(upload(B.pair_edges, T.pair_edges, s));
-  DS3_TRY(upload(B.pair_ij, T.pair_ij, s));
-  DS3_TRY(upload(B.anchor, T.anchor, s));
-  return DS3_OK;
+  TableUpload u;
+  u.add(B.edges, T.edges);
+  u.add(B.kf_off, T.kf_off);
+  u.add(B.kf_npx, T.kf_npx);
+  u.add(B.node_ptr, T.node_ptr);
+  u.add(B.node_adj, T.node_adj);
+  u.add(B.pair_ptr, T.pair_ptr);
+  u.add(B.pair_edges, T.pair_edges);
+  u.add(B.pair_ij, T.pair_ij);
+  u.add(B.anchor, T.anchor);
+  return u.flush(s);
 }
 
 constexpr int kPlainPPT = 16;

@@ -88,14 +88,15 @@ static size_t carve_match(void* base, int64_t ray_px, int64_t tmp_idx, int n_dir
   W.range = c.take<float>(size_t(std::max<int64_t>(ray_px, 1)));
   W.conf = c.take<float>(size_t(std::max<int64_t>(ray_px, 1)));
   W.idx_tmp = c.take<int32_t>(size_t(std::max<int64_t>(tmp_idx, 1)));
+  // the tables of run_match, in its order
   W.dirs = c.take<MatchDir>(std::max(n_dirs, 1));
   W.md = c.take<MutualDir>(std::max(n_sides, 1));
   W.prefix_m = c.take<int32_t>(size_t(n_dirs) + 1);
   W.prefix_u = c.take<int32_t>(size_t(n_sides) + 1);
+  W.nu_sides = c.take<NuSide>(std::max(n_sides, 1));
   W.step_stripes = c.take<unsigned>(size_t(kStepStripes) * kStripeStride);
   // every side has at most npx / 256 + 1 tiles and the sides' pixels add up to tmp_idx
   W.part = c.take<unsigned>(size_t(std::max<int64_t>(tmp_idx / 256 + n_sides + 1, 1)));
-  W.nu_sides = c.take<NuSide>(std::max(n_sides, 1));
   return c.used;
 }
 
@@ -124,10 +125,13 @@ struct EdgeSpec {
   int64_t out_off;         // output offset (idx, valid)
 };
 
-static int run_match(const std::vector<EdgeSpec>& es, const void* cross, ds3_dtype dt, const MatchConst& C,
+static int run_match(const std::vector<EdgeSpec>& es, const void* kf_arena, int64_t ray_px, const void* cross, ds3_dtype dt,
+                     const MatchConst& C,
                      double nu_min, MatchWs& W, int32_t* idx_out, uint8_t* valid_out, float* nu,
                      int32_t* admit, uint64_t* lm_steps, ds3_timer* timer, hipStream_t s) {
   const int ne = int(es.size());
+  // the ray images need no tables: they are under way while the host makes them
+  DS3_TRY(launch_raymap(kf_arena, ray_px, nullptr, 0, dt, W.rays, W.range, W.conf, s));
   std::vector<MatchDir> dirs;
   std::vector<MutualDir> sides;
   bool big = false;
@@ -156,11 +160,13 @@ static int run_match(const std::vector<EdgeSpec>& es, const void* cross, ds3_dty
   ItemMap map_u = make_map(assign_parts(sides.data(), int(sides.size()), per_u, nu_sides.data()), prefix_u);
   map_m.prefix = W.prefix_m;
   map_u.prefix = W.prefix_u;
-  DS3_TRY(upload(W.dirs, dirs, s));
-  DS3_TRY(upload(W.prefix_m, prefix, s));
-  DS3_TRY(upload(W.md, sides, s));
-  DS3_TRY(upload(W.prefix_u, prefix_u, s));
-  DS3_TRY(upload(W.nu_sides, nu_sides, s));
+  TableUpload u;
+  u.add(W.dirs, dirs);
+  u.add(W.md, sides);
+  u.add(W.prefix_m, prefix);
+  u.add(W.prefix_u, prefix_u);
+  u.add(W.nu_sides, nu_sides);
+  DS3_TRY(u.flush(s));
   unsigned* stripes = lm_steps ? W.step_stripes : nullptr;
   if (stripes) DS3_TRY(launch_fill_u32(stripes, size_t(kStepStripes) * kStripeStride, 0u, s));
   DS3_TRY(timer_record(timer, true, s));
@@ -169,16 +175,6 @@ static int run_match(const std::vector<EdgeSpec>& es, const void* cross, ds3_dty
   if (stripes) DS3_TRY(launch_sum_stripes(stripes, reinterpret_cast<unsigned long long*>(lm_steps), s));
   DS3_TRY(launch_mutual(W.md, map_u, per_u, C, W.idx_tmp, idx_out, valid_out, W.part, s));
   return launch_nu(W.part, W.nu_sides, ne, nu_min, nu, admit, s);
-}
-
-static int check_arch_local() {
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return fail(DS3_EHIP, "no HIP device");
-  hipDeviceProp_t prop;
-  if (hipGetDeviceProperties(&prop, dev) != hipSuccess) return fail(DS3_EHIP, "hipGetDeviceProperties");
-  if (std::strncmp(prop.gcnArchName, "gfx950", 6) != 0)
-    return fail(DS3_ENOTSUP, std::string("libds3 is built for gfx950, device is ") + prop.gcnArchName);
-  return DS3_OK;
 }
 
 }  // namespace ds3
@@ -205,7 +201,7 @@ int ds3_match(const void* ref_xyzc, ds3_image ref, const void* qry_xyzc, ds3_ima
   DS3_TRY(check_image(ref, true));
   DS3_TRY(check_image(qry, false));
   if (ws_bytes < ds3_match_workspace_bytes(ref.H, ref.W)) return fail(DS3_ENOSPACE, "match: workspace");
-  DS3_TRY(check_arch_local());
+  DS3_TRY(check_arch());
   hipStream_t s = S(stream);
   const int pxb = dtype == DS3_F32 ? 16 : 8;
   const char* rp = static_cast<const char*>(ref_xyzc) + ref.px_offset * pxb;
@@ -238,7 +234,7 @@ int ds3_match_bidir(const void* X_ii, const void* X_ji, const void* X_jj, const 
   DS3_TRY(check_image(img_j, true));
   if (ws_bytes < ds3_match_bidir_workspace_bytes(img_i.H, img_i.W, img_j.H, img_j.W))
     return fail(DS3_ENOSPACE, "match_bidir: workspace");
-  DS3_TRY(check_arch_local());
+  DS3_TRY(check_arch());
   hipStream_t s = S(stream);
   const int64_t ni = int64_t(img_i.H) * img_i.W, nj = int64_t(img_j.H) * img_j.W;
   MatchWs W;
@@ -294,7 +290,7 @@ int ds3_match_batch(const void* kf_arena, const ds3_image* kf, int32_t n_kf, con
   const size_t need = ds3_match_batch_workspace_bytes(n_kf, kf, n_edges, edges);
   if (need == 0) return fail(DS3_EINVAL, "match_batch: bad edge table");
   if (ws_bytes < need) return fail(DS3_ENOSPACE, "match_batch: workspace");
-  DS3_TRY(check_arch_local());
+  DS3_TRY(check_arch());
   hipStream_t s = S(stream);
   int64_t ray_px = 0, tmp = 0;
   for (int k = 0; k < n_kf; ++k) ray_px = std::max(ray_px, kf[k].px_offset + int64_t(kf[k].H) * kf[k].W);
@@ -320,8 +316,7 @@ int ds3_match_batch(const void* kf_arena, const ds3_image* kf, int32_t n_kf, con
   }
   MatchWs W;
   carve_match(workspace, ray_px, tmp, 2 * n_edges, 2 * n_edges, n_edges, W);
-  DS3_TRY(launch_raymap(kf_arena, ray_px, nullptr, 0, dtype, W.rays, W.range, W.conf, s));
-  return run_match(es, cross_arena, dtype, make_match_const(*params), params->nu_min, W, idx_arena,
+  return run_match(es, kf_arena, ray_px, cross_arena, dtype, make_match_const(*params), params->nu_min, W, idx_arena,
                    valid_arena, nu, admit, lm_steps, match_timer, s);
 }
 
@@ -381,7 +376,7 @@ int ds3_gauge_align(const void* X_i, ds3_image img_i, const void* X_j, ds3_image
   if (ws_bytes < gauge_ws_bytes()) return fail(DS3_ENOSPACE, "gauge_align: workspace");
   DS3_TRY(check_image(img_i, false));
   DS3_TRY(check_image(img_j, false));
-  DS3_TRY(check_arch_local());
+  DS3_TRY(check_arch());
   const int pxb = dtype == DS3_F32 ? 16 : 8;
   const char* pi = static_cast<const char*>(X_i) + img_i.px_offset * pxb;
   const char* pj = static_cast<const char*>(X_j) + img_j.px_offset * pxb;
@@ -392,7 +387,7 @@ int ds3_gauge_align(const void* X_i, ds3_image img_i, const void* X_j, ds3_image
 
 int ds3_apply_gauge(double* poses, int32_t n_kf, const uint8_t* mask, const double* T, void* stream) {
   if (!poses || !mask || !T || n_kf < 0) return fail(DS3_EINVAL, "apply_gauge: bad arguments");
-  DS3_TRY(check_arch_local());
+  DS3_TRY(check_arch());
   return launch_apply_gauge(poses, n_kf, mask, T, S(stream));
 }
 
@@ -406,7 +401,7 @@ int ds3_gauge_sync(double* poses, int32_t n_kf, const int32_t* agent_of_kf, cons
     return fail(DS3_EINVAL, "gauge_sync: null pointer");
   if (n_kf <= 0 || n_edges < 0) return fail(DS3_EINVAL, "gauge_sync: bad sizes");
   if (ws_bytes < ds3_gauge_workspace_bytes(n_kf)) return fail(DS3_ENOSPACE, "gauge_sync: workspace");
-  DS3_TRY(check_arch_local());
+  DS3_TRY(check_arch());
   hipStream_t s = S(stream);
   Carver w(workspace);
   void* gws = w.take<char>(gauge_ws_bytes());

@@ -5,6 +5,7 @@
 
 #include <cstddef>
 #include <cstdint>
+#include <cstring>
 #include <string>
 #include <vector>
 
@@ -49,6 +50,33 @@ struct Carver {
     used = off + count * sizeof(T);
     return base ? reinterpret_cast<T*>(base + off) : nullptr;
   }
+};
+
+// Fails unless the current device is a gfx950.
+int check_arch();
+
+// Tables that lie one after the other in a workspace, uploaded in one copy (the copy is staged before flush returns).
+// Each small copy costs the host about 4 us and the stream a command of its own.
+class TableUpload {
+ public:
+  template <class T>
+  void add(T* dst, const std::vector<T>& src) {
+    if (src.empty()) return;
+    char* d = reinterpret_cast<char*>(dst);
+    if (!first_) first_ = d;
+    const size_t at = size_t(d - first_);  // the tables are added in the order in which they lie
+    bytes_.resize(at + src.size() * sizeof(T));
+    std::memcpy(bytes_.data() + at, src.data(), src.size() * sizeof(T));
+  }
+  int flush(hipStream_t s) {
+    if (!first_) return DS3_OK;
+    return check_hip(hipMemcpyAsync(first_, bytes_.data(), bytes_.size(), hipMemcpyHostToDevice, s),
+                     "hipMemcpyAsync(tables)");
+  }
+
+ private:
+  char* first_ = nullptr;
+  std::vector<char> bytes_;
 };
 
 // ---- graph-step device structures --------------------------------------------------------------------

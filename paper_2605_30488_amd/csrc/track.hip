@@ -190,8 +190,10 @@ static int track_impl(const void* arena, ds3_dtype dtype, const ds3_track_proble
   if (ws_bytes < carve_track(nullptr, n, tiles, dtype, B)) return fail(DS3_ENOSPACE, "track: workspace too small");
   carve_track(workspace, n, tiles, dtype, B);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  DS3_TRY_HIP(hipMemcpyAsync(B.edges, edges.data(), sizeof(EdgeDev) * n, hipMemcpyHostToDevice, s));
-  DS3_TRY_HIP(hipMemcpyAsync(B.items, items.data(), sizeof(WorkItem) * tiles, hipMemcpyHostToDevice, s));
+  TableUpload u;
+  u.add(B.edges, edges);
+  u.add(B.items, items);
+  DS3_TRY(u.flush(s));
   const int seg = kReduceThreads * kTrackPPT;
   const GnConst c = make_gn_const(*gn);
   TrackConst tc;
