@@ -217,6 +217,10 @@ __device__ inline void track_step(const EdgeDev& E, int p, const float* partials
     if (!stop) {
       double tau[7];
       st.status = solve7(st.H, st.b, st.lam, tc.eps0, tc.eps_mult, tc.attempts, tau);
+      // The pose is computed as from stored values: without this the compiler fuses the last products of the solve into
+      // the first sums of the exponential, and decisions between nearly equal costs rest on the last bits.
+#pragma unroll
+      for (int k = 0; k < 7; ++k) asm volatile("" : "+v"(tau[k]));
       for (int k = 0; k < 7; ++k) st.tau[k] = tau[k];
       const Sim3 Tt = sim3_mul(sim3_exp(tau), sim3_load(st.T));
       Sim3 Tn = Tt;
