@@ -125,12 +125,15 @@ __device__ inline void acc_ray_row(Acc& a, const float* J, float W, float e) {
   }
 }
 
+__device__ inline float clamp01(float x) { return __builtin_amdgcn_fmed3f(x, 0.0f, 1.0f); }
+
 // One match after its checks: x = T_ij X_j (d2 = |x|^2 > 0), X_i with di2 = |X_i|^2 > 0 and
 // sq = (C_i C_j)^(1/4): e of eq. (1), whitening, Huber weights, J_x, accumulation.
 __device__ inline void acc_core(Acc& a, float x0, float x1, float x2, float d2, float xi0, float xi1, float xi2,
                                 float di2, float sq, const GnConst& k) {
-  const float rd = rsqrtf(d2);
-  const float rdi = rsqrtf(di2);
+  // both above 1e-18, where the instruction alone is what rsqrtf computes (its scaling is for denormal numbers)
+  const float rd = __builtin_amdgcn_rsqf(d2);
+  const float rdi = __builtin_amdgcn_rsqf(di2);
   const float d = d2 * rd;
   const float di = di2 * rdi;
   const float p0 = x0 * rd, p1 = x1 * rd, p2 = x2 * rd;
@@ -145,11 +148,12 @@ __device__ inline void acc_core(Acc& a, float x0, float x1, float x2, float d2, 
   const float r3 = sq * k.inv_sd * e3;
   const float a0 = fabsf(r0), a1 = fabsf(r1), a2 = fabsf(r2), a3 = fabsf(r3);
   // IRLS weight min(1, kappa/|r|); the reciprocal is the hardware one (1 ulp)
-  // (min(1, kappa * rcp(|r|)): |r| = 0 gives rcp = inf and weight 1)
-  const float w0 = fminf(1.0f, k.kappa * __builtin_amdgcn_rcpf(a0));
-  const float w1 = fminf(1.0f, k.kappa * __builtin_amdgcn_rcpf(a1));
-  const float w2 = fminf(1.0f, k.kappa * __builtin_amdgcn_rcpf(a2));
-  const float w3 = fminf(1.0f, k.kappa * __builtin_amdgcn_rcpf(a3));
+  // (min(1, kappa * rcp(|r|)): |r| = 0 gives rcp = inf and weight 1; the product is positive, so the minimum is the
+  // multiply's clamp to [0, 1])
+  const float w0 = clamp01(k.kappa * __builtin_amdgcn_rcpf(a0));
+  const float w1 = clamp01(k.kappa * __builtin_amdgcn_rcpf(a1));
+  const float w2 = clamp01(k.kappa * __builtin_amdgcn_rcpf(a2));
+  const float w3 = clamp01(k.kappa * __builtin_amdgcn_rcpf(a3));
   // rho(r) = t (|r| - t/2) with t = w |r|: r^2/2 inside kappa, kappa |r| - kappa^2/2 outside
   const float t0 = w0 * a0, t1 = w1 * a1, t2 = w2 * a2, t3 = w3 * a3;
   a.cost += t0 * fmaf(-0.5f, t0, a0) + t1 * fmaf(-0.5f, t1, a1) + t2 * fmaf(-0.5f, t2, a2) +
@@ -739,38 +743,90 @@ __global__ __launch_bounds__(kReduceThreads) void k_reduce_stream(const void* __
   const int cnt = seg_count[seg];
   Acc a;
   acc_zero(a);
+  // (not with the float64 cost: its sum, on whose last bits decisions rest, would be contracted another way)
+  constexpr bool kSmallRec = sizeof(rec_t) == 16 && !C64;
+  GnConst kv = k;
+  if constexpr (kSmallRec) {
+    // constants of the loop, as far as the registers go (see in_vgpr; all of M and of k: 311 us instead of 301)
+#pragma unroll
+    for (int q = 9; q < 12; ++q) in_vgpr(M[q]);
+    in_vgpr(kv.kappa);
+  }
+  auto one = [&](const float* xj, const float* xi, float sq) {
+    float x0, x1, x2;
+    transform(M, xj[0], xj[1], xj[2], x0, x1, x2);
+    if constexpr (MODE == kCalibrated) {
+      // xi holds the target (u_m, v_m, 1/z_i[m])
+      if (x2 > 1e-9f && x2 < __builtin_huge_valf() && isfinite(x0) && isfinite(x1))
+        acc_core_cal(a, x0, x1, x2, xi[0], xi[1], xi[2], sq, Ki, lim, kv);
+    } else {
+      const float d2 = fmaf(x0, x0, fmaf(x1, x1, x2 * x2));
+      if (d2 > 1e-18f && d2 < __builtin_huge_valf()) {
+        const float di2 = fmaf(xi[0], xi[0], fmaf(xi[1], xi[1], xi[2] * xi[2]));
+        acc_core(a, x0, x1, x2, d2, xi[0], xi[1], xi[2], di2, sq, kv);
+        if constexpr (C64) c64 += cost_f64(M64, xj, xi, sq, kv);
+      }
+    }
+  };
   // U records in flight per thread: a ring of U registers, each refilled with the record U groups ahead as
   // soon as its current record has been taken, so that U loads are outstanding while one record is computed
   // (deeper rings cost 4 registers per record, not a second copy of the arithmetic's registers)
+  constexpr int kGroup = kReduceThreads * U;
   rec_t buf[U];
+  if constexpr (kSmallRec) {
+    // Bound by the vector units' issue. Whole groups go without a compare per record; a record is unpacked before its
+    // refill, which then needs no registers of its own and no copies that wait for it. 800 edges (74 M records): 325 us
+    // with compares, copies and scalar operands in every record, now 301 us.
+    auto load_at = [&](uint32_t q) {
+      return Rec<DT>::load(reinterpret_cast<const rec_t*>(reinterpret_cast<const char*>(in) + q * uint32_t(sizeof(rec_t))));
+    };
+    const uint32_t last = uint32_t(max(cnt - 1, 0));  // a segment without records still has its place in the stream
 #pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const int q = u * kReduceThreads + int(threadIdx.x);
-    if (q < cnt) buf[u] = Rec<DT>::load(in + q);
-  }
+    for (int u = 0; u < U; ++u) buf[u] = load_at(min(uint32_t(u * kReduceThreads) + threadIdx.x, last));
+    int k0 = 0;
 #pragma unroll 1
-  for (int k0 = 0; k0 < cnt; k0 += kReduceThreads * U) {
+    for (; k0 + kGroup <= cnt; k0 += kGroup) {
+      const bool next_whole = k0 + 2 * kGroup <= cnt;  // uniform
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        uint32_t q = uint32_t(k0 + kGroup + u * kReduceThreads) + threadIdx.x;
+        if (!next_whole) q = min(q, last);  // past the end: the last record again
+        float xj[3], xi[3], sq;
+        Rec<DT>::unpack(buf[u], xj, xi, sq);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          in_vgpr(xj[c]);
+          in_vgpr(xi[c]);
+        }
+        in_vgpr(sq);
+        buf[u] = load_at(q);
+        one(xj, xi, sq);
+      }
+    }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int q = k0 + u * kReduceThreads + int(threadIdx.x);
-      const rec_t r = buf[u];
-      if (q + kReduceThreads * U < cnt) buf[u] = Rec<DT>::load(in + q + kReduceThreads * U);
-      if (q < cnt) {
-        float xj[3], xi[3], sq;
-        Rec<DT>::unpack(r, xj, xi, sq);
-        float x0, x1, x2;
-        transform(M, xj[0], xj[1], xj[2], x0, x1, x2);
-        if constexpr (MODE == kCalibrated) {
-          // xi holds the target (u_m, v_m, 1/z_i[m])
-          if (x2 > 1e-9f && x2 < __builtin_huge_valf() && isfinite(x0) && isfinite(x1))
-            acc_core_cal(a, x0, x1, x2, xi[0], xi[1], xi[2], sq, Ki, lim, k);
-        } else {
-          const float d2 = fmaf(x0, x0, fmaf(x1, x1, x2 * x2));
-          if (d2 > 1e-18f && d2 < __builtin_huge_valf()) {
-            const float di2 = fmaf(xi[0], xi[0], fmaf(xi[1], xi[1], xi[2] * xi[2]));
-            acc_core(a, x0, x1, x2, d2, xi[0], xi[1], xi[2], di2, sq, k);
-            if constexpr (C64) c64 += cost_f64(M64, xj, xi, sq, k);
-          }
+      float xj[3], xi[3], sq;
+      Rec<DT>::unpack(buf[u], xj, xi, sq);
+      if (k0 + u * kReduceThreads + int(threadIdx.x) < cnt) one(xj, xi, sq);
+    }
+  } else {
+    // Bound by memory; a record is what it unpacks to, and more registers would cost a wave per SIMD.
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int q = u * kReduceThreads + int(threadIdx.x);
+      if (q < cnt) buf[u] = Rec<DT>::load(in + q);
+    }
+#pragma unroll 1
+    for (int k0 = 0; k0 < cnt; k0 += kGroup) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int q = k0 + u * kReduceThreads + int(threadIdx.x);
+        const rec_t r = buf[u];
+        if (q + kGroup < cnt) buf[u] = Rec<DT>::load(in + q + kGroup);
+        if (q < cnt) {
+          float xj[3], xi[3], sq;
+          Rec<DT>::unpack(r, xj, xi, sq);
+          one(xj, xi, sq);
         }
       }
     }
