@@ -192,9 +192,9 @@ __device__ inline int32_t match_query(const RayImage& R, float4 x, float u, floa
       break;
     }
     const float step = fmaxf(fabsf(un - u), fabsf(vn - v));
-    // A step that does not move (singular system, clamped or vanishing step) samples the same point: the same cost, so
-    // it is rejected.
-    if (cn < c) {
+    // A step that does not move (singular system, clamped or vanishing step) is rejected. Its cost is no test of that: c may
+    // be of the first cell's differences and cn of a later fetch of the same cell, rounded otherwise and then below c.
+    if (cn < c && (un != u || vn != v)) {
       u = un;
       v = vn;
       c = cn;
