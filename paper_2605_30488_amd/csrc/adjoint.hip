@@ -260,14 +260,14 @@ __global__ __launch_bounds__(kAdjThreads) void k_adjoint_scatter_i(
       }
     }
     wm[lane] = m;
-    __builtin_amdgcn_wave_barrier();  // a wave's LDS writes are ordered before its reads
+    wave_sync();
 #pragma unroll
     for (int r = 0; r < 3; ++r) {
       const int q = r * kWave + lane, px = q / 3;
       const int32_t mp = wm[px];
       if (mp >= 0) atomicAdd(gi + 3 * int64_t(mp) + (q - 3 * px), wg[q]);
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
   }
 }
 

@@ -83,6 +83,15 @@ __device__ inline double wave_sum(double v) {
   return v;
 }
 
+// Orders a wave's LDS accesses: what its lanes wrote before is read by the others after, and what they read before is
+// overwritten after. The barrier alone keeps the wave's instructions together but orders no memory access for the compiler;
+// the fences add no instruction, since a wave's LDS accesses are performed as they are issued.
+__device__ inline void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 __device__ inline int wave_sum(int v) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
