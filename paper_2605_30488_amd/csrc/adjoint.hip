@@ -143,7 +143,7 @@ __device__ inline void wave_store8(const float* v, int lane, float* __restrict__
   if (lane < 8) out[(b0 ? 4 : 0) + (b1 ? 2 : 0) + (b2 ? 1 : 0)] = s;
 }
 
-// Query side, gathered: block (tile, k) owns 2048 pixels of keyframe k and walks the edges that end in
+// Query side, gathered: block (tile, k) owns 512 pixels of keyframe k and walks the edges that end in
 // k (j = k). Per pixel it sums dE/dX_k = (s_ij R_ij)^T dE/dx and the j half of dE/dC over those edges in
 // registers and stores them once (zeros where nothing contributes); per (edge, tile) it leaves the
 // seven pose-tangent pieces [g; x cross g; x . g] in part7 (row stride `stride` tiles).

@@ -3,7 +3,6 @@
 
 #include <algorithm>
 #include <cmath>
-#include <cstring>
 #include <numeric>
 #include <vector>
 
@@ -116,8 +115,6 @@ static std::vector<int32_t> assign_parts(MutualDir* sides, int n, int per, NuSid
 
 // Shared driver: ray images, both directions of every edge, mutual check, nu.
 struct EdgeSpec {
-  const void* ref_i;  // canonical arena of i (pixel 0)
-  const void* ref_j;
   int64_t ray_i, ray_j;   // pixel offsets of the two ray images in W.rays
   int64_t q_ji, q_ij;     // pixel offsets of the cross-view pointmaps in their arena
   int Hi, Wi, Hj, Wj;
@@ -295,14 +292,11 @@ int ds3_match_batch(const void* kf_arena, const ds3_image* kf, int32_t n_kf, con
   int64_t ray_px = 0, tmp = 0;
   for (int k = 0; k < n_kf; ++k) ray_px = std::max(ray_px, kf[k].px_offset + int64_t(kf[k].H) * kf[k].W);
   std::vector<EdgeSpec> es(n_edges);
-  const int pxb = dtype == DS3_F32 ? 16 : 8;
   for (int e = 0; e < n_edges; ++e) {
     const ds3_image &I = kf[edges[e].i], &J = kf[edges[e].j];
     if (cross_off[2 * e] < 0 || cross_off[2 * e + 1] < 0 || edges[e].idx_offset < 0)
       return fail(DS3_EINVAL, "match_batch: negative offset");
     EdgeSpec& E = es[e];
-    E.ref_i = static_cast<const char*>(kf_arena) + I.px_offset * pxb;
-    E.ref_j = static_cast<const char*>(kf_arena) + J.px_offset * pxb;
     E.ray_i = I.px_offset;
     E.ray_j = J.px_offset;
     E.q_ji = cross_off[2 * e];

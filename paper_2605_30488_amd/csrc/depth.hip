@@ -125,8 +125,9 @@ __global__ __launch_bounds__(kDepthThreads) void k_dr_logrange(const void* __res
   }
 }
 
-// Correctly rounded a / d from r = recip_f64(d) (the last step of a division, without its scaling: for d, and any a with
-// |a| <= |d|, far from the ends of the range; a quotient that underflows may lose its last bits).
+// Correctly rounded a / d from r = recip_f64(d): two Newton-Raphson steps on the estimate of 1 / d, then Markstein's
+// correction of the quotient by its residual (a division without its scaling: for d, and any a with |a| <= |d|, far from the
+// ends of the range; a quotient that underflows may lose its last bits).
 __device__ inline double recip_f64(double d) {
   double y = __builtin_amdgcn_rcp(d);
   y = fma(y, fma(-d, y, 1.0), y);

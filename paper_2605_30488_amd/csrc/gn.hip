@@ -860,7 +860,11 @@ __global__ __launch_bounds__(kReduceThreads) void k_reduce_stream(const void* __
 // --------------------------------------------------------------------------------------------------
 constexpr int kRoles = 3;
 
-// Stores v at p by an exchange at device scope and waits until it has been performed.
+// Stores v at p by an exchange at device scope and waits until it has been performed: its result comes back from where
+// all XCDs' device-scope accesses of p are performed, so one that is issued after the wait, by any block, sees v. That
+// is a property of this chip; the memory model would have the order from a release at the ticket and an acquire after it,
+// which write back and invalidate an L2 each time: 342 us instead of 339 for a call of one 512 x 384 frame, 412 instead of
+// 393 for four, 561 instead of 466 for 128 frames of 96 x 64.
 template <class T>
 __device__ inline void publish(T* p, T v) {
   T was = __hip_atomic_exchange(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

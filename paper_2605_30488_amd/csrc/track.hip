@@ -77,9 +77,13 @@ namespace ds3 {
 constexpr int kTrackPPT = 16;  // segment = 4096 frame pixels
 
 // Calls with at most this many segments run each round as one launch of three blocks per segment (k_track_round).
-// us per call, 512 x 384 float32 frames of 48 segments, one launch against two: 338 to 457 (1 frame), 330 to 439 (2),
-// 391 to 460 (4), 491 to 506 (6), 530 to 509 (8). Beyond one block per CU the records that each role reads again cost
-// more than the launch.
+// us per call, one launch against two (float32; bfloat16 agrees within 10%, but for 498 to 464 at five frames):
+//   512 x 384 frames (48 segments): 1 frame 338 to 435, 3 frames 374 to 449, 4: 403 to 445, 5: 417 to 451, 8: 527 to 498
+//   128 x 96 frames (3 segments): 1 frame 308 to 411, 32 frames 370 to 446, 53: 383 to 448, 64: 434 to 448, 85: 561 to 454
+//   64 x 48 frames (1 segment): 1 frame 283 to 332, 96 frames 357 to 392, 160: 338 to 401, 192: 458 to 406, 256: 437 to 411
+// Up to 170 segments, two blocks per CU, one launch gains with frames of any size. Past that the records that each role
+// reads again begin to cost more than the launch: whole frames, as online tracking has them, still gain up to about this
+// limit (a block per CU in the two-launch form's reduction), many short ones lose 3 to 20% there.
 constexpr int kRoundItems = 256;
 
 struct TrackBuffers {
