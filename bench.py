@@ -51,31 +51,31 @@ TRAFFIC = {
     "k_reduce_stream": {
         "sources": ["paper_2605_30488_amd/csrc/gn.hip", "paper_2605_30488_amd/csrc/common.hpp",
                     "paper_2605_30488_amd/csrc/internal.hpp"],
-        "configs": [4], "sha": "72fda60aba693063", "bytes": 1145452134},
+        "configs": [4], "sha": "fcb26ae34d1b4868", "bytes": 1145925632},
     "k_reduce_stream (calibrated)": {
         "sources": ["paper_2605_30488_amd/csrc/gn.hip", "paper_2605_30488_amd/csrc/common.hpp",
                     "paper_2605_30488_amd/csrc/internal.hpp"],
-        "configs": [3, 4], "sha": "72fda60aba693063", "bytes": 2331345203},
+        "configs": [3, 4], "sha": "fcb26ae34d1b4868", "bytes": 2329939763},
     "k_reduce_stream (tracker, float64 cost)": {
         "sources": ["paper_2605_30488_amd/csrc/gn.hip", "paper_2605_30488_amd/csrc/common.hpp",
                     "paper_2605_30488_amd/csrc/internal.hpp", "paper_2605_30488_amd/csrc/track.hip"],
-        "configs": [4], "sha": "1da38c2b3d8c901f", "bytes": 344525926},
+        "configs": [4], "sha": "890de6b115c8b038", "bytes": 344524698},
     "k_match_batched": {
         "sources": ["paper_2605_30488_amd/csrc/match.hip", "paper_2605_30488_amd/csrc/match_internal.hpp",
                     "paper_2605_30488_amd/csrc/common.hpp"],
-        "configs": [3, 4], "sha": "503738ea23f6298d", "bytes": 9307983565},
+        "configs": [3, 4], "sha": "05d573e080088b4d", "bytes": 9323667149},
     "k_adjoint_gather": {
         "sources": ["paper_2605_30488_amd/csrc/adjoint.hip", "paper_2605_30488_amd/csrc/common.hpp",
                     "paper_2605_30488_amd/csrc/internal.hpp"],
-        "configs": [5], "sha": "1cc5a7c4e673eb35", "bytes": 21995653325},
+        "configs": [5], "sha": "e6fc24353e7a0abf", "bytes": 21747664691},
     "k_fuse": {
         "sources": ["paper_2605_30488_amd/csrc/fuse.hip", "paper_2605_30488_amd/csrc/common.hpp",
                     "paper_2605_30488_amd/csrc/internal.hpp", "paper_2605_30488_amd/csrc/sim3.hpp"],
-        "configs": [3, 4], "sha": "7fbaa408e40ffed6", "bytes": 1651931034},
+        "configs": [3, 4], "sha": "eea106ab25915160", "bytes": 1651929190},
     "k_dr_data": {
         "sources": ["paper_2605_30488_amd/csrc/depth.hip", "paper_2605_30488_amd/csrc/common.hpp",
                     "paper_2605_30488_amd/csrc/internal.hpp"],
-        "configs": [4], "sha": "daf3551665166184", "bytes": 2785748173},
+        "configs": [4], "sha": "9f2254777d22051b", "bytes": 1697060557},
 }
 
 
@@ -517,7 +517,7 @@ def measure_depth(g, W, dev, start, with_cpu=True, iters=10, reps=3):
     k_ms = float(np.mean(kms))
     px_valid = int((W.idx >= 0).sum().item())
     px_bytes = 16 if W.dtype == "f32" else 8
-    kbytes = 4 * info["px_scanned"] + (2 * px_bytes + 8) * px_valid
+    kbytes = 4 * info["px_scanned"] + (2 * px_bytes + 4) * px_valid  # matches; points and 16-bit slots
     gbs = kbytes / (k_ms * 1e-3) / 1e9
     eta = plan.eta()
     res = {"segmentation_ms": round(seg_ms, 2), "segments": info["segments"],

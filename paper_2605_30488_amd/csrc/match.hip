@@ -295,8 +295,8 @@ __device__ inline bool locate_item(const ItemMap& M, int b, int& entry, int& ite
 // summed per block and added to one of kStepStripes counters 128 B apart (block b to stripe b mod
 // kStepStripes): a single counter hit by every wave becomes a hot spot of one L2 channel that stalls the
 // whole launch.
-// Bound by the gathers: a search is 5.5 cells in a chain, and the L1's return path is busy 89% of the time at 6.6 waves
-// per SIMD. 800 edges (276e6 queries) of a 200-keyframe graph: 4.1 ms with one tile per block of four waves (a search of
+// Bound by the gathers: a search is 5.5 cells in a chain, and the L1's return path is busy 87% of the time (35% waiting for
+// the L2) at 6.6 waves per SIMD, with a vector instruction every 3.3 cycles; 9.3 GB from memory are no limit. 800 edges (276e6 queries) of a 200-keyframe graph: 4.1 ms with one tile per block of four waves (a search of
 // the item map, the tables and the queries' latency per 64 queries), 16-byte rays and the references unsorted; 3.5 ms
 // with four tiles per block and 12-byte rays; 3.35 ms with a wave per block. Tried without effect: the queries past the
 // L2, the texels as 12 + 12 bytes (8 + 8 + 8: 3.7 ms).
@@ -387,9 +387,10 @@ int launch_sum_stripes(const unsigned* step_stripes, unsigned long long* out, hi
 // blocks of one side would otherwise all hit one counter), then k_nu sums each side in a fixed order.
 // --------------------------------------------------------------------------------------------------
 // One block: `per` runs of kMutualPx pixels, one after the other; the next run's forward matches and confidences are loaded
-// before the current one's gathers. Bound by the gathers' latency (the L1 waits for the L2 77% of the time); both sides of
-// an edge run on one XCD and share its L2. 276e6 pixels of 800 edges: 1.07 ms with one run per block (the map's lookup,
-// the tables and the first loads are a chain of their own), 0.86 ms with eight; 0.71 ms of it without the confidences.
+// before the current one's gathers. Bound by memory: 4.3 GB (the L1 waits for the L2 68% of the time) at 5.0 TB/s, as a large
+// copy; both sides of an edge run on one XCD and share its L2. 276e6 pixels of 800 edges: 1.07 ms with one run per block
+// (the map's lookup, the tables and the first loads are a chain of their own), 0.86 ms with eight; 0.71 ms without the
+// confidences.
 __device__ inline void mutual_tiles_of(const MutualDir& M, int item, int per, const MatchConst& P,
                                        const int32_t* __restrict__ idx_tmp, int32_t* __restrict__ idx_final,
                                        uint8_t* __restrict__ valid, unsigned* __restrict__ part) {
